@@ -137,8 +137,8 @@ int qd_gate_class(const double* U, int32_t dT);
  *   QD_ROUTE_TILED   slices staged in LDS (a target with a small stride);
  *   QD_ROUTE_DIAG    elementwise phases (diagonal U);
  *   QD_ROUTE_GEMM    dense 10 <= d_T <= 64 (and other monomials in that range): per tile of
- *                    slices a small complex GEMM, U and the tile in LDS;
- *   QD_ROUTE_GENERIC any d_T up to 1024 or D >= 2^32 (U in device memory).
+ *                    slices a complex GEMM on the matrix cores, the tile in LDS;
+ *   QD_ROUTE_GENERIC any d_T up to 1024 (the same kernel) or D >= 2^32 (a 64-bit kernel).
  * Validation as in qd_apply_gate. */
 int qd_gate_route(const int32_t* dims, int32_t n, int32_t prec, const int32_t* targets, int32_t k,
                   const int32_t* controls, const int32_t* control_values, int32_t m, const double* U,

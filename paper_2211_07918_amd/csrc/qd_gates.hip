@@ -5,7 +5,7 @@
 // That is the Kronecker-embedded Moment operator I (x) U (x) I of Sec. 3.5 applied to the state
 // vector, at O(D d_T) cost.
 //
-// Kernel families (each HBM-bound: at most 8 d_T flops per 2 x 16 bytes moved):
+// Kernel families (HBM-bound up to d_T of about 32: 8 d_T flops per 2 x 16 bytes moved):
 //   k_slices_direct  one slice per thread. Used when every target has a stride >= run_min (or at
 //                    least one line, for controls inside a line that leave lines inactive), so the
 //                    lanes of a wavefront take consecutive low digits and each load instruction
@@ -15,8 +15,9 @@
 //                    each slice inside LDS and writes the tile back coalesced.
 //   k_diag           diagonal gates (Z_d, controlled phases): elementwise, consecutive lanes on
 //                    consecutive amplitudes whatever the target strides.
-//   k_dense_generic  any d_T <= 1024 and any register size (64-bit indices): slices gathered into
-//                    LDS, U read from device memory.
+//   k_dense_mfma     dense gates of d_T >= 10: tiles of slices as complex GEMMs on the matrix cores.
+//   k_dense_generic  registers of 2^32 amplitudes or more (64-bit indices), any d_T <= 1024: slices
+//                    gathered into LDS, U read from device memory.
 // The slice kernels take U (dense) or a destination/phase table (monomial: X_{+a}, controlled
 // shifts, qudit swaps) inside the kernel arguments.
 #include <hip/hip_runtime.h>
@@ -582,146 +583,164 @@ __global__ __launch_bounds__(256) void k_dense_generic(R* psi_raw, const unsigne
   }
 }
 
-// ------------------------------------------------------------------------------------------ gemm
-// Dense gates with kGemmMin <= d_T <= kGemmMax on registers below 2^32 amplitudes: per tile of ns
-// slices, Y = U X as a small complex GEMM. U (zero-padded to dP = d_T rounded up to a multiple of 4,
-// rows kGemmPad elements apart so the rows a wavefront reads fall in different banks) and the
-// tile's X (dP rows x ns slices) sit in LDS; each thread accumulates a 4 x 4 block of outputs in
-// registers; the results go back through LDS, so loads and stores both run over consecutive
-// slices. Workgroups are persistent and stage U once.
+// ------------------------------------------------------------------------------------------ matrix cores
+// Dense gates with d_T >= kGemmMin on registers below 2^32 amplitudes: per tile of ns slices,
+// Y = U X as a complex GEMM on the matrix cores in the state's own precision (16x16x4 FP64 or FP32
+// products: FP64 inputs and sums for complex128, FP32 for complex64; four products per complex one).
+// Bound: HBM up to d_T of about 32, the matrix cores above (8 d_T flops per 2 x 16 bytes; 72 TFLOP/s
+// FP64 as a large product reaches it on this card).
+//   - X (all d_T amplitudes of ns slices) is staged in LDS once, pitch ns + 1 so that both loading
+//     orders and the operand reads spread over the banks; every output of those slices is made by
+//     this workgroup, so the results go from the accumulators straight back to HBM.
+//   - U is stored by the host in operand order (lane l of K step k holds row l & 15, column
+//     4 k + (l >> 4)), one coalesced 16-byte (8-byte) load per lane and step, four steps ahead. It is
+//     read from L2 by every workgroup: at 16 slices or more per tile that is at most 1 KB per 256
+//     matrix-core cycles of a SIMD. So U takes no LDS and d_T is bounded by X alone.
+//   - A job is one 16-row tile of U times CG column tiles; the waves of a workgroup share them.
+// The operands of a product may change places, which transposes the result: with kYF the 16
+// consecutive lanes of a store hold consecutive target combinations (a target has the smallest
+// stride) instead of consecutive slices, so both kinds of gate store runs.
+// Measured, complex128 (kernel time; before: a vector-unit GEMM with U and X in LDS up to d_T = 64,
+// above it a kernel that read U from L2 for every product): on 3^14 amplitudes d_T = 27 76 -> 49 us,
+// 81 880 -> 92 us, 243 5220 -> 195 us (48 TFLOP/s); on 4^12 amplitudes d_T = 64 360 -> 189 us, 256
+// 16.4 -> 0.60 ms (57 TFLOP/s); on the hybrid register of 1.1e8 amplitudes d_T = 27 1083 -> 757 us
+// (4.5 TB/s), 54 2160 -> 1119 us. complex64 on 4^12: 64 205 -> 110 us, 256 15.2 -> 0.34 ms.
 constexpr int kGemmMin = 10;
 constexpr int kGemmMax = 64;
-constexpr int kGemmOut = 4096;        // outputs per tile (dP x ns), 16 per thread
-// The tile moves between HBM and LDS element by element in one of two orders: slices fastest (the
-// free digits hold the smallest stride), or target combinations fastest in ascending offset (a
-// target holds the smallest stride), so that consecutive lanes touch neighbouring amplitudes.
-struct GemmHead {
+
+struct MfmaArgs {
   SliceMap sm;                        // slices: the non-target digits (controls fixed)
-  Magic32 nsm;                        // division by ns
-  Magic32 dpm;                        // division by dP
-  int32_t dT, dP, ns, yfast;
-  // followed by int64_t toff[dT], int32_t yord[dP] (target combinations by ascending offset, then
-  // the padding rows) and 2 dP^2 values of R (U zero-padded, row-major)
+  Magic32 div;                        // division by ns, or by KP when target combinations are fastest
+  uint32_t dT, KP, RT, ns, njobs;     // KP: d_T rounded up to 4; RT: 16-row tiles of U; jobs per tile
+  const unsigned char* desc;          // int64_t toff[d_T] by ascending offset, then (16-byte aligned)
+                                      // RT x KP/4 x 64 entries of U in operand order, in that order
 };
 
-template <typename R>
-__global__ __launch_bounds__(256) void k_dense_gemm(R* psi_raw, const unsigned char* desc) {
+template <typename R> struct Mfma16;
+template <> struct Mfma16<double> {
+  typedef double V4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ V4 mul(double a, double b, V4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ uint32_t row(uint32_t i, uint32_t q) { return 4u * i + q; }
+};
+template <> struct Mfma16<float> {
+  typedef float V4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ V4 mul(float a, float b, V4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ uint32_t row(uint32_t i, uint32_t q) { return 4u * q + i; }
+};
+
+template <typename R, int CG, bool YF>
+__global__ __launch_bounds__(1024) void k_dense_mfma(R* psi_raw, MfmaArgs a) {
   using C = typename CxT<R>::T;
+  using M = Mfma16<R>;
+  using V4 = typename M::V4;
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  const GemmHead& h = *reinterpret_cast<const GemmHead*>(desc);
-  // the head is read into locals and LDS before the first store: read later from global memory it
-  // would be fetched again by vector loads (the stores could alias it)
-  __shared__ SliceMap smap;
-  static_assert(sizeof(SliceMap) % 4 == 0, "slice map copied in 4-byte words");
-  for (uint32_t i = threadIdx.x; i < sizeof(SliceMap) / 4; i += blockDim.x)
-    reinterpret_cast<uint32_t*>(&smap)[i] = reinterpret_cast<const uint32_t*>(&h.sm)[i];
-  const Magic32 nsm = h.nsm, dpm = h.dpm;
-  const uint32_t dT = uint32_t(h.dT), dP = uint32_t(h.dP), ns = uint32_t(h.ns), ldu = dP + 1;
-  const uint32_t count = h.sm.count;
   C* __restrict__ psi = reinterpret_cast<C*>(psi_raw);
-  C* xs = reinterpret_cast<C*>(lds_raw);                        // dP x ns, element (y, j) at y ns + j
-  C* us = xs + dP * ns;                                         // dP x dP, row stride ldu
-  int64_t* sb = reinterpret_cast<int64_t*>(us + dP * ldu);     // ns slice bases
-  int64_t* to = sb + ns;                                        // dT target offsets
-  int32_t* yo = reinterpret_cast<int32_t*>(to + dT);            // dP rows in memory order
-  const int64_t* tg = reinterpret_cast<const int64_t*>(desc + sizeof(GemmHead));
-  const int32_t* yg = reinterpret_cast<const int32_t*>(desc + sizeof(GemmHead) + sizeof(int64_t) * dT);
-  const R* ug = reinterpret_cast<const R*>(desc + sizeof(GemmHead) + sizeof(int64_t) * dT + sizeof(int32_t) * dP);
-  const bool yfast = h.yfast != 0;
-  const uint32_t tid = threadIdx.x;
-  for (uint32_t i = tid; i < dP * dP; i += blockDim.x) {
-    const uint32_t r = i / dP, c = i - r * dP;
-    C v;
-    v.x = ug[2 * i];
-    v.y = ug[2 * i + 1];
-    us[r * ldu + c] = v;
-  }
-  for (uint32_t i = tid; i < dT; i += blockDim.x) to[i] = tg[i];
-  for (uint32_t i = tid; i < dP; i += blockDim.x) yo[i] = yg[i];
-  const uint32_t rbn = dP / 4, nblk = rbn * (ns / 4);
-  const uint32_t rb = tid % rbn, kb = tid / rbn;                // this thread's 4 x 4 output block
-  const uint32_t ntiles = (count + ns - 1) / ns;
-  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint32_t s0 = tile * ns;
-    __syncthreads();   // U staged; the previous tile is stored
-    for (uint32_t j = tid; j < ns; j += blockDim.x) sb[j] = s0 + j < count ? sm_offset(smap, s0 + j) : int64_t(-1);
-    __syncthreads();
-    // every load of the tile in flight before the first LDS write (at most kGemmOut / 256 each)
-    {
-      constexpr int EPT = kGemmOut / 256;
-      const uint32_t tot = dP * ns;
-      C v[EPT];
-      uint32_t at[EPT];
+  const uint32_t dT = a.dT, KP = a.KP, ns = a.ns, P = ns + 1, bs = blockDim.x, tid = threadIdx.x;
+  C* xs = reinterpret_cast<C*>(lds_raw);                        // KP x ns, element (y, j) at y P + j
+  int64_t* sb = reinterpret_cast<int64_t*>(xs + KP * P + (KP * P & 1u));   // ns slice bases
+  int64_t* to = sb + ns;                                        // d_T target offsets
+  const int64_t* tg = reinterpret_cast<const int64_t*>(a.desc);
+  const C* ug = reinterpret_cast<const C*>(a.desc + ((sizeof(int64_t) * dT + 15) & ~size_t(15)));
+  const uint32_t s0 = blockIdx.x * ns, nsv = min(ns, a.sm.count - s0);   // nsv: slices of this tile
+  // a column past the last slice repeats it (read, multiplied and not stored): no load is conditional
+  for (uint32_t j = tid; j < ns; j += bs) sb[j] = sm_offset(a.sm, s0 + min(j, nsv - 1));
+  for (uint32_t i = tid; i < dT; i += bs) to[i] = tg[i];
+  __syncthreads();
+  constexpr int B = 8;   // loads in flight per thread
+  const uint32_t tot = KP * ns;
+  for (uint32_t e0 = tid; e0 < tot; e0 += B * bs) {
+    C v[B];
+    uint32_t at[B];
+    int64_t off[B];
+    bool pad[B];
 #pragma unroll
-      for (int k = 0; k < EPT; ++k) {
-        const uint32_t e = tid + uint32_t(k) * 256u;
-        v[k].x = R(0);
-        v[k].y = R(0);
-        at[k] = 0xFFFFFFFFu;
-        if (e < tot) {
-          uint32_t y, j;
-          if (yfast) {
-            j = magic_div(e, dpm);
-            y = uint32_t(yo[e - j * dP]);
-          } else {
-            y = magic_div(e, nsm);
-            j = e - y * ns;
-          }
-          at[k] = y * ns + j;
-          if (y < dT && sb[j] >= 0) v[k] = ld_stream(psi + (sb[j] + to[y]));
+    for (int k = 0; k < B; ++k) {
+      const uint32_t e = min(e0 + uint32_t(k) * bs, tot - 1);   // past the end: the last element again
+      const uint32_t q = magic_div(e, a.div), r = e - q * a.div.d;
+      const uint32_t y = YF ? r : q, j = YF ? q : r;
+      pad[k] = y >= dT;
+      at[k] = y * P + j;
+      off[k] = sb[j] + to[pad[k] ? dT - 1 : y];
+    }
+#pragma unroll
+    for (int k = 0; k < B; ++k) v[k] = ld_stream(psi + off[k]);
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+      if (pad[k]) v[k].x = v[k].y = R(0);
+      xs[at[k]] = v[k];
+    }
+  }
+  __syncthreads();
+  const uint32_t lane = tid & 63u, lq = lane >> 4, lr = lane & 15u, nw = bs >> 6;
+  const uint32_t KS = KP / 4;
+  for (uint32_t job = tid >> 6; job < a.njobs; job += nw) {   // wave-uniform
+    const uint32_t cj = job / a.RT, rt = job - cj * a.RT;
+    const C* up = ug + size_t(rt) * KS * 64 + lane;
+    const C* xp = xs + lq * P + cj * (16u * CG) + lr;
+    V4 re[CG], im[CG];
+#pragma unroll
+    for (int g = 0; g < CG; ++g) {
+      re[g] = V4{R(0), R(0), R(0), R(0)};
+      im[g] = re[g];
+    }
+    auto ldu = [&](C (&u)[4], uint32_t k0) {   // four steps of U (past the last one: that one again)
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k) u[k] = up[64 * min(k0 + k, KS - 1)];
+    };
+    auto step = [&](C u, uint32_t ks) {
+      C x[CG];
+#pragma unroll
+      for (int g = 0; g < CG; ++g) x[g] = xp[ks * 4 * P + 16 * g];
+#pragma unroll
+      for (int g = 0; g < CG; ++g) {
+        re[g] = YF ? M::mul(x[g].x, u.x, re[g]) : M::mul(u.x, x[g].x, re[g]);
+        im[g] = YF ? M::mul(x[g].y, u.x, im[g]) : M::mul(u.x, x[g].y, im[g]);
+      }
+#pragma unroll
+      for (int g = 0; g < CG; ++g) {
+        re[g] = YF ? M::mul(x[g].y, -u.y, re[g]) : M::mul(-u.y, x[g].y, re[g]);
+        im[g] = YF ? M::mul(x[g].x, u.y, im[g]) : M::mul(u.y, x[g].x, im[g]);
+      }
+    };
+    auto four = [&](const C (&u)[4], uint32_t k0) {
+#pragma unroll
+      for (uint32_t k = 0; k < 4; ++k)
+        if (k0 + k < KS) step(u[k], k0 + k);
+    };
+    C ua[4], ub[4];
+    ldu(ua, 0);
+    for (uint32_t ks = 0; ks < KS; ks += 8) {
+      ldu(ub, ks + 4);
+      four(ua, ks);
+      ldu(ua, ks + 8);
+      four(ub, ks + 4);
+    }
+    // lane lr of a store holds consecutive slices (or consecutive target combinations): the four rows
+    // of a register tile are four stores
+    int64_t ro[4];
+    bool rv[4];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) {
+      const uint32_t y = rt * 16u + (YF ? lr : M::row(i, lq));
+      rv[i] = y < dT;
+      ro[i] = to[min(y, dT - 1)];
+    }
+#pragma unroll
+    for (int g = 0; g < CG; ++g) {
+      const uint32_t c0 = (cj * CG + uint32_t(g)) * 16u;
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) {
+        const uint32_t j = c0 + (YF ? M::row(i, lq) : lr);
+        const int64_t o = sb[min(j, ns - 1)] + ro[i];
+        C v;
+        v.x = re[g][i];
+        v.y = im[g][i];
+        if (rv[i] && j < nsv) {
+          // runs of target combinations end inside lines, which the cache merges across row tiles
+          if constexpr (YF) psi[o] = v;
+          else st_stream(psi + o, v);
         }
       }
-#pragma unroll
-      for (int k = 0; k < EPT; ++k)
-        if (at[k] != 0xFFFFFFFFu) xs[at[k]] = v[k];
-    }
-    __syncthreads();
-    C acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        acc[i][k].x = R(0);
-        acc[i][k].y = R(0);
-      }
-    if (tid < nblk) {
-      const C* ur = us + 4 * rb * ldu;
-      const C* xc = xs + 4 * kb;
-      for (uint32_t c = 0; c < dP; ++c) {
-        C u[4], x[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) u[i] = ur[i * ldu + c];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = xc[c * ns + k];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            acc[i][k].x = fma(u[i].x, x[k].x, acc[i][k].x);
-            acc[i][k].x = fma(-u[i].y, x[k].y, acc[i][k].x);
-            acc[i][k].y = fma(u[i].x, x[k].y, acc[i][k].y);
-            acc[i][k].y = fma(u[i].y, x[k].x, acc[i][k].y);
-          }
-      }
-    }
-    __syncthreads();   // every product has read X
-    if (tid < nblk) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) xs[(4 * rb + i) * ns + 4 * kb + k] = acc[i][k];
-    }
-    __syncthreads();
-    for (uint32_t e = tid; e < dP * ns; e += blockDim.x) {
-      uint32_t y, j;
-      if (yfast) {
-        j = magic_div(e, dpm);
-        y = uint32_t(yo[e - j * dP]);
-      } else {
-        y = magic_div(e, nsm);
-        j = e - y * ns;
-      }
-      if (y < dT && sb[j] >= 0) st_stream(psi + (sb[j] + to[y]), xs[y * ns + j]);
     }
   }
 }
@@ -741,7 +760,7 @@ template <int KIND, typename R, int DT = 0, typename OP = void, int SPT = 0, int
 static const char* label() {
   static thread_local char buf[160] = {0};
   if (!buf[0]) {
-    static const char* kn[] = {"k_slices_direct", "k_slices_tiled", "k_diag", "k_dense_generic", "k_dense_gemm",
+    static const char* kn[] = {"k_slices_direct", "k_slices_tiled", "k_diag", "k_dense_generic", "k_dense_mfma",
                                "k_slices_direct_lu"};
     static const char* modes[] = {"plain", "pred", "edge"};
     const char* rn = real_name<R>();
@@ -1198,65 +1217,122 @@ static int launch_direct_lu(qd_state* s, const GatePlan& p) {
   return check_launch("k_slices_direct_lu");
 }
 
+// Tile of the matrix-core kernel: ns slices (a multiple of 16), CG column tiles per job and the waves
+// of a workgroup. X takes KP (ns + 1) amplitudes of LDS: the widest tile within 40 KB (four workgroups
+// per CU, so that one's loads and stores overlap the others' products), else the widest within 80 KB
+// (two per CU), else 16 slices in up to 150 KB; where fewer than two workgroups per CU would be left the
+// tile is halved. One case lies beyond that: complex128 with d_T > 568 holds 8 slices.
+struct MfmaTile {
+  uint32_t ns = 0, lds = 0;
+  int cg = 1, waves = 4;
+};
+
+static MfmaTile mfma_tile(uint32_t dT, uint32_t KP, size_t amp, uint64_t count) {
+  auto bytes = [&](uint32_t ns) { return size_t(KP) * (ns + 1) * amp + amp + sizeof(int64_t) * (ns + dT); };
+  MfmaTile t;
+  for (size_t cap : {size_t(40) << 10, size_t(80) << 10, size_t(150) << 10}) {
+    for (uint32_t ns : {128u, 64u, 32u, 16u})
+      if (bytes(ns) <= cap) {
+        t.ns = ns;
+        break;
+      }
+    if (t.ns) break;
+  }
+  if (!t.ns) t.ns = 8;
+  while (t.ns > 16 && (count + t.ns - 1) / t.ns < 512) t.ns /= 2;
+  t.lds = uint32_t(bytes(t.ns));
+  const uint32_t RT = (dT + 15) / 16, CT = std::max(1u, t.ns / 16);
+  double best = 0.0;
+  for (int cg : {2, 1}) {
+    if (uint32_t(cg) > CT) continue;
+    for (int w : {16, 8, 4}) {
+      const uint32_t jobs = RT * (CT / cg), rounds = (jobs + w - 1) / w;
+      if ((w > 4 && jobs < uint32_t(w)) || (w == 16 && t.lds < (uint32_t(80) << 10))) continue;
+      const double eff = double(jobs) / double(rounds * w);   // share of the waves at work
+      if (eff > best + 0.05) {
+        best = eff;
+        t.cg = cg;
+        t.waves = w;
+      }
+    }
+  }
+  return t;
+}
+
 template <typename R>
 static int launch_gemm(qd_state* s, const GatePlan& p) {
+  using C = typename CxT<R>::T;
   const Register& r = s->reg;
   int role[QD_MAX_QUDITS] = {};
   for (int j = 0; j < p.k; ++j) role[p.targets[j]] = 1;
   for (int j = 0; j < p.m; ++j) role[p.controls[j]] = 1;
   int64_t base = 0;
   for (int j = 0; j < p.m; ++j) base += int64_t(p.cvals[j]) * r.strides[p.controls[j]];
-  const int dT = p.dT, dP = (dT + 3) / 4 * 4, ns = (kGemmOut / dP) / 4 * 4;
-  const size_t bytes = sizeof(GemmHead) + sizeof(int64_t) * size_t(dT) + sizeof(int32_t) * size_t(dP) +
-                       sizeof(R) * 2 * size_t(dP) * dP;
-  std::vector<unsigned char> buf(bytes, 0);
-  auto* h = reinterpret_cast<GemmHead*>(buf.data());
   const std::vector<Group> groups = make_groups(r, role, nullptr, 0, r.n);
-  if (fill_slicemap(groups, base, &h->sm) != QD_OK) return launch_generic<R>(s, p);
-  h->nsm = make_magic32(uint32_t(ns));
-  h->dpm = make_magic32(uint32_t(dP));
-  h->dT = dT;
-  h->dP = dP;
-  h->ns = ns;
-  int64_t* toff = reinterpret_cast<int64_t*>(buf.data() + sizeof(GemmHead));
-  target_offsets(r, p, toff);
-  int32_t* yord = reinterpret_cast<int32_t*>(buf.data() + sizeof(GemmHead) + sizeof(int64_t) * size_t(dT));
-  for (int y = 0; y < dP; ++y) yord[y] = y;
-  std::sort(yord, yord + dT, [&](int32_t a, int32_t b) { return toff[a] < toff[b]; });
+  MfmaArgs a;
+  if (int(groups.size()) > kMaxGroups || fill_slicemap(groups, base, &a.sm) != QD_OK) return launch_generic<R>(s, p);
+  if (a.sm.count == 0) return QD_OK;
+  const uint32_t dT = uint32_t(p.dT), KP = (dT + 3) / 4 * 4, KS = KP / 4, RT = (dT + 15) / 16;
+  const MfmaTile t = mfma_tile(dT, KP, sizeof(C), a.sm.count);
+  const uint64_t ntiles = (uint64_t(a.sm.count) + t.ns - 1) / t.ns;
   int64_t tmin = INT64_MAX;
   for (int j = 0; j < p.k; ++j) tmin = std::min<int64_t>(tmin, r.strides[p.targets[j]]);
-  h->yfast = groups.empty() || tmin < groups[0].stride ? 1 : 0;   // groups[0]: the lowest free run
-  R* U = reinterpret_cast<R*>(buf.data() + sizeof(GemmHead) + sizeof(int64_t) * size_t(dT) + sizeof(int32_t) * size_t(dP));
-  for (int a = 0; a < dT; ++a)
-    for (int c = 0; c < dT; ++c) {
-      U[2 * (size_t(a) * dP + c)] = R(p.U[2 * (size_t(a) * dT + c)]);
-      U[2 * (size_t(a) * dP + c) + 1] = R(p.U[2 * (size_t(a) * dT + c) + 1]);
-    }
-  if (h->sm.count == 0) return QD_OK;
-  void* dev = nullptr;
-  int rc = ring_push(s, buf.data(), bytes, &dev);
+  const bool yf = groups.empty() || tmin < groups[0].stride;   // groups[0]: the lowest free run
+  a.dT = dT;
+  a.KP = KP;
+  a.RT = RT;
+  a.ns = t.ns;
+  a.njobs = RT * (std::max(1u, t.ns / 16) / uint32_t(t.cg));
+  a.div = make_magic32(yf ? KP : t.ns);
+  // the target combinations by ascending offset: rows and columns of U in that order
+  std::vector<int64_t> toff(dT);
+  target_offsets(r, p, toff.data());
+  std::vector<int32_t> ord(dT);
+  std::iota(ord.begin(), ord.end(), 0);
+  std::sort(ord.begin(), ord.end(), [&](int32_t x, int32_t y) { return toff[x] < toff[y]; });
+  const size_t uoff = (sizeof(int64_t) * dT + 15) & ~size_t(15);
+  const size_t bytes = uoff + sizeof(C) * size_t(RT) * KS * 64;
+  char* host = nullptr;
+  char* dev = nullptr;
+  int rc = ring_reserve(&s->ring, s->stream, bytes, &host, &dev);
   if (rc) return rc;
-  using C = typename CxT<R>::T;
-  const size_t lds = size_t(dP) * ns * sizeof(C) + size_t(dP) * (dP + 1) * sizeof(C) + sizeof(int64_t) * size_t(ns + dT) +
-                     sizeof(int32_t) * size_t(dP);
-  auto k = k_dense_gemm<R>;
-  QD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-  int dev_id = 0, cus = 256, per_cu = 0;
-  (void)hipGetDevice(&dev_id);
-  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev_id);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, 256, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-  const uint64_t ntiles = (uint64_t(h->sm.count) + ns - 1) / ns;
-  const unsigned grid = unsigned(std::min<uint64_t>(ntiles, uint64_t(cus) * per_cu));
-  hipLaunchKernelGGL(k, dim3(grid), dim3(256), lds, s->stream, reinterpret_cast<R*>(s->data),
-                     static_cast<const unsigned char*>(dev));
+  int64_t* tg = reinterpret_cast<int64_t*>(host);
+  for (uint32_t i = 0; i < dT; ++i) tg[i] = toff[ord[i]];
+  C* ug = reinterpret_cast<C*>(host + uoff);
+  for (uint32_t rt = 0; rt < RT; ++rt)
+    for (uint32_t ks = 0; ks < KS; ++ks)
+      for (uint32_t l = 0; l < 64; ++l) {
+        const uint32_t row = rt * 16 + (l & 15u), col = ks * 4 + (l >> 4);
+        C v;
+        v.x = v.y = R(0);
+        if (row < dT && col < dT) {
+          const double* e = p.U.data() + 2 * (size_t(ord[row]) * dT + ord[col]);
+          v.x = R(e[0]);
+          v.y = R(e[1]);
+        }
+        *ug++ = v;
+      }
+  rc = ring_commit(&s->ring, s->stream, host, dev, bytes);
+  if (rc) return rc;
+  a.desc = reinterpret_cast<const unsigned char*>(dev);
+  auto launch = [&](auto k) -> int {
+    if (t.lds > (size_t(64) << 10))
+      QD_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, int(t.lds)));
+    hipLaunchKernelGGL(k, dim3(unsigned(ntiles)), dim3(64 * t.waves), t.lds, s->stream, reinterpret_cast<R*>(s->data), a);
+    return check_launch("k_dense_mfma");
+  };
   g_last_kernel = label<kKnGemm, R>();
-  return check_launch("k_dense_gemm");
+  if (t.cg == 2) return yf ? launch(k_dense_mfma<R, 2, true>) : launch(k_dense_mfma<R, 2, false>);
+  return yf ? launch(k_dense_mfma<R, 1, true>) : launch(k_dense_mfma<R, 1, false>);
 }
 
 template <typename R>
 static int launch_gate_t(qd_state* s, const GatePlan& p) {
   const int route = route_gate(s->reg, s->prec, p);
-  if (route == QD_ROUTE_GENERIC) return launch_generic<R>(s, p);
+  // the generic kernel is left with registers of 2^32 amplitudes or more (launch_gemm also hands it
+  // gates whose free digits fall into more groups than a slice map holds)
+  if (route == QD_ROUTE_GENERIC)
+    return uint64_t(s->reg.D) <= 0xFFFFFFFFull && p.dT >= kGemmMin ? launch_gemm<R>(s, p) : launch_generic<R>(s, p);
   if (route == QD_ROUTE_GEMM) return launch_gemm<R>(s, p);
   if (route == QD_ROUTE_DIAG) return launch_diag<R>(s, p);
   // On the slice-per-thread kernel a monomial U up to d_T = 9 runs as a dense one: each thread then

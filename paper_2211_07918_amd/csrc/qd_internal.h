@@ -139,6 +139,9 @@ namespace qd {
 // Reserve `bytes` in the state's parameter ring, copy `src` there and return the device address.
 // Wrapping around synchronises the stream first so no in-flight copy reads recycled memory.
 int ring_push(qd_state* s, const void* src, size_t bytes, void** dev_out);
+// ring_reserve / ring_commit: the same in two steps, for parameters written straight into the ring.
+int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out, char** dev_out);
+int ring_commit(ParamRing* r, hipStream_t stream, const char* host, char* dev, size_t bytes);
 int ring_push_stream(ParamRing* r, hipStream_t stream, const void* src, size_t bytes, void** dev_out);
 void ring_free(ParamRing* r);
 

@@ -339,7 +339,7 @@ void fill_slicemap64(const std::vector<Group>& g, int64_t base, SliceMap64* sm) 
 }
 
 // ------------------------------------------------------------------------------------------ param ring
-int ring_push_stream(ParamRing* r, hipStream_t stream, const void* src, size_t bytes, void** dev_out) {
+int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out, char** dev_out) {
   const size_t align = 256;
   const size_t need = (bytes + align - 1) / align * align;
   if (!r->host || need > r->cap) {
@@ -359,11 +359,24 @@ int ring_push_stream(ParamRing* r, hipStream_t stream, const void* src, size_t b
     QD_HIP(hipStreamSynchronize(stream));
     r->head = 0;
   }
-  std::memcpy(r->host + r->head, src, bytes);
-  QD_HIP(hipMemcpyAsync(r->dev + r->head, r->host + r->head, bytes, hipMemcpyHostToDevice, stream));
+  *host_out = r->host + r->head;
   *dev_out = r->dev + r->head;
   r->head += need;
   return QD_OK;
+}
+
+int ring_commit(ParamRing*, hipStream_t stream, const char* host, char* dev, size_t bytes) {
+  QD_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, stream));
+  return QD_OK;
+}
+
+int ring_push_stream(ParamRing* r, hipStream_t stream, const void* src, size_t bytes, void** dev_out) {
+  char *host = nullptr, *dev = nullptr;
+  int rc = ring_reserve(r, stream, bytes, &host, &dev);
+  if (rc) return rc;
+  std::memcpy(host, src, bytes);
+  *dev_out = dev;
+  return ring_commit(r, stream, host, dev, bytes);
 }
 
 int ring_push(qd_state* s, const void* src, size_t bytes, void** dev_out) {

@@ -432,6 +432,40 @@ def test_gemm_route_sizes(stream, prec):
 
 
 @pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("dims, t, c, v", [
+    ((2, 11, 2, 5, 3, 7, 2, 3, 2, 5, 3), (1,), (), ()),            # d_T = 11: 128 slices a tile, ragged
+    ((2, 11, 2, 5, 3, 7, 2, 3, 2, 5, 3), (9, 10), (0,), (1,)),     # d_T = 15, lowest targets, a control
+    ((17, 2, 3, 5, 2, 3, 7, 2, 3, 2), (0,), (), ()),               # one past a 16-row tile, 32 slices a tile
+    ((3, 13, 5, 2, 7, 2, 3), (1, 2), (6,), (2,)),                  # 65, a control below one line
+    ((4, 3, 9, 9, 2, 5), (2, 3), (), ()),                          # 81
+    ((3, 13, 15, 2, 2), (2, 1), (4,), (0,)),                       # 195, targets not in offset order
+    ((2, 17, 17, 2), (1, 2), (), ()),                              # 289: more than one workgroup of 8 waves
+    ((2, 8, 71, 3), (1, 2), (), ()),                               # 568: the last with 16 slices in LDS
+    ((3, 13, 15, 2, 2), (0, 1, 2), (), ()),                        # 585: 8 slices a tile, half of it used
+    ((3, 4, 4, 4, 4, 4), (5, 1, 2, 3, 4), (), ()),                 # 1024, every slice of three amplitudes apart
+])
+def test_dense_on_the_matrix_cores(stream, prec, dims, t, c, v):
+    """k_dense_mfma at the edges of its tiles, d_T from 11 to 1024, against the oracle. One gate adds
+    at most about c d_T u to the 2-norm: 1e-12 covers it in FP64, c64_tol in FP32."""
+    rng = C.seeded_rng(93)
+    D = O.register_size(dims)
+    psi0 = rng.standard_normal(D) + 1j * rng.standard_normal(D)
+    psi0 /= np.linalg.norm(psi0)
+    dT = int(np.prod([dims[q] for q in t]))
+    U = C.haar_unitary(dT, rng)
+    s = Q.qd_state_init(dims, prec, stream)
+    try:
+        Q.qd_state_upload(s, psi0)
+        Q.qd_apply_gate_ex(s, t, c, v, U, Q.QD_FLAG_SKIP_UNITARY_CHECK)
+        assert Q.qd_last_kernel().startswith("k_dense_mfma")
+        out = Q.qd_state_download(s)
+    finally:
+        Q.qd_state_free(s)
+    ref = O.apply_gate(psi0, dims, t, c, v, U)
+    assert max_abs(out, ref) <= (1e-12 if prec == Q.QD_C128 else c64_tol(1, dT)), (t, c, dT, prec)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
 def test_dense_12_16_one_slice_per_thread(stream, prec):
     """Dense gates of d_T = 12 and 16 whose targets all have large strides run one slice per thread
     with U in LDS (route DIRECT), with and without a control; each against the oracle."""
