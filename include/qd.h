@@ -96,8 +96,9 @@ const char* qd_last_error(void);
  * profiling labels; it changes no state. */
 const char* qd_last_kernel(void);
 
-/* Gate kernel launches made on a state since it was created: one per qd_apply_gate that moved
- * data, and one per pass of the density-matrix calls (a composed run of operations is one pass).
+/* Gate passes made on a state since it was created: one per qd_apply_gate that moved data, one per
+ * gate of qd_circuit_apply and one per pass of the density-matrix calls (a composed run of operations
+ * is one pass), also where one launch carries several of them.
  * Host counter, no synchronisation. QD_EINVAL for a null argument. */
 int qd_state_gate_launches(const qd_state* s, int64_t* out);
 
@@ -385,8 +386,10 @@ int qd_circuit_moments(const qd_circuit* c, int32_t* moment_out, int32_t* depth)
  * chained control has no level v_i + 1. Other gates are copied. */
 int qd_circuit_decompose(const qd_circuit* c, qd_circuit** out);
 
-/* Apply the circuit's gates in order to a state of the same register (qd_apply_gate for each).
- * QD_EDIM if the registers differ. Asynchronous, like qd_apply_gate. */
+/* Apply the circuit's gates in order to a state of the same register (as qd_apply_gate for each;
+ * gates whose targets fit one window of the register share a pass over the state, and gates that
+ * commute exactly may change places). QD_EDIM if the registers differ. Asynchronous, like
+ * qd_apply_gate. */
 int qd_circuit_apply(qd_state* s, const qd_circuit* c);
 
 void qd_circuit_free(qd_circuit* c);
@@ -540,7 +543,9 @@ typedef struct {
  * controls together span qudits S with prod d_S <= 4 (a gate and the channels that follow it, a
  * qubit-controlled gate on a qubit and its channel, operations on two qubits) is composed on the
  * host in FP64: each operation embedded on S (a gate as its controlled unitary, the identity
- * elsewhere), then one pass of the product superoperator on (S, S + n). Asynchronous.
+ * elsewhere), then one pass of the product superoperator on (S, S + n). Passes whose qudits fit one
+ * window of the register share one trip over rho, and ones that commute exactly may change places.
+ * Asynchronous.
  * A call that fails validation leaves rho unchanged; an allocation or launch failure in a later
  * pass of a call (QD_ENOMEM, QD_EDEVICE) can leave rho with the earlier passes applied, as can such
  * a failure in the second pass of a two-pass qd_density_apply_gate. */

@@ -16,7 +16,8 @@
 //   * consecutive operations whose targets and controls together span qudits Sq of dimension
 //     <= kFuseGroup are composed on the host into one superoperator on (Sq, Sq + n), each embedded
 //     on Sq, and applied in one pass.
-// Both run through the library's gate kernels (HBM-bound passes over the D^2 elements). The
+// Both run through the library's gate kernels (HBM-bound passes over the D^2 elements); operations
+// that follow one another share a pass where their qudits fit one window (apply_gate_list). The
 // readouts here (outer product, diagonal, trace, <psi|rho|psi>) are HBM-bound kernels of their own.
 #include <hip/hip_runtime.h>
 
@@ -238,6 +239,75 @@ static std::vector<double> embed_on(const Register& phys, const qd_density_op& o
   return W;
 }
 
+static int run_list(qd_state* rho, const std::vector<SparseGate>& list) {
+  std::vector<GateRef> refs;
+  for (const SparseGate& g : list) refs.push_back(ref_of(g));
+  return apply_gate_list(rho, refs);
+}
+
+static int checked(SparseGate&& g, std::vector<SparseGate>* list) {
+  for (double x : g.U)
+    if (!std::isfinite(x)) return fail(QD_ENOTUNITARY, "U has a NaN or Inf entry");
+  list->push_back(std::move(g));
+  return QD_OK;
+}
+
+// a validated gate of the physical register as one or two gates of the doubled one
+static int append_gate(const Register& phys, int n, const int32_t* targets, int32_t k, const int32_t* controls,
+                       const int32_t* control_values, int32_t m, const double* U, std::vector<SparseGate>* list) {
+  int dT = 1;
+  for (int j = 0; j < k; ++j) dT *= phys.dims[targets[j]];
+  int dC = 1;
+  for (int j = 0; j < m; ++j) dC *= phys.dims[controls[j]];
+  const int dG = dT * dC;                 // the gate embedded on (targets, controls)
+  const int cls = classify(U, dT);
+  const bool one_pass = cls == QD_CLASS_DIAGONAL ? dG <= kOnePass : (m == 0 && dT <= kOnePass);
+  if (one_pass) {
+    // one pass of G (x) conj(G) over (T, C, T + n, C + n), G[(t, c), (t', c')] = delta(c, c') times
+    // U[t][t'] when the control digits c hold the control values, else delta(t, t')
+    std::vector<double> G(2 * size_t(dG) * dG, 0.0);
+    int vidx = 0;                          // local index of the control values (first control most significant)
+    for (int j = 0; j < m; ++j) vidx = vidx * phys.dims[controls[j]] + control_values[j];
+    for (int c = 0; c < dC; ++c)
+      for (int t = 0; t < dT; ++t)
+        for (int t1 = 0; t1 < dT; ++t1) {
+          const size_t o = 2 * (size_t(t * dC + c) * dG + size_t(t1 * dC + c));
+          if (c == vidx) {
+            G[o] = U[2 * (t * dT + t1)];
+            G[o + 1] = U[2 * (t * dT + t1) + 1];
+          } else if (t == t1) {
+            G[o] = 1.0;
+          }
+        }
+    SparseGate g;
+    g.t.assign(targets, targets + k);
+    g.t.insert(g.t.end(), controls, controls + m);
+    for (int j = 0; j < k + m; ++j) g.t.push_back(g.t[size_t(j)] + n);
+    g.U = superoperator(G.data(), 1, dG);   // element ((a, b), (c, d)) = G[a][c] conj(G[b][d])
+    return checked(std::move(g), list);
+  }
+  SparseGate g, h;
+  g.t.assign(targets, targets + k);
+  g.c.assign(controls, controls + m);
+  g.v.assign(control_values, control_values + m);
+  g.U.assign(U, U + 2 * size_t(dT) * dT);
+  h = g;
+  for (int32_t& q : h.t) q += n;
+  for (int32_t& q : h.c) q += n;
+  for (size_t i = 1; i < h.U.size(); i += 2) h.U[i] = -h.U[i];
+  const int rc = checked(std::move(g), list);
+  return rc ? rc : checked(std::move(h), list);
+}
+
+// a superoperator S on the physical qudits q, as a gate of the doubled register
+static int append_super(int n, const int32_t* q, int32_t k, std::vector<double>&& S, std::vector<SparseGate>* list) {
+  SparseGate g;
+  g.t.assign(q, q + k);
+  for (int j = 0; j < k; ++j) g.t.push_back(q[j] + n);
+  g.U = std::move(S);
+  return checked(std::move(g), list);
+}
+
 }  // namespace dm
 }  // namespace qd
 
@@ -285,57 +355,9 @@ int qd_density_apply_gate(qd_state* rho, const int32_t* targets, int32_t k, cons
   if (rc) return rc;
   rc = validate_gate(phys, targets, k, controls, control_values, m, U, flags);
   if (rc) return rc;
-  int dT = 1;
-  for (int j = 0; j < k; ++j) dT *= phys.dims[targets[j]];
-  int dC = 1;
-  for (int j = 0; j < m; ++j) dC *= phys.dims[controls[j]];
-  const int dG = dT * dC;                 // the gate embedded on (targets, controls)
-  const uint32_t skip = flags | QD_FLAG_SKIP_UNITARY_CHECK;
-  const int cls = classify(U, dT);
-  const bool one_pass = cls == QD_CLASS_DIAGONAL ? dG <= kOnePass : (m == 0 && dT <= kOnePass);
-  if (one_pass) {
-    // one pass of G (x) conj(G) over (T, C, T + n, C + n), G[(t, c), (t', c')] = delta(c, c') times
-    // U[t][t'] when the control digits c hold the control values, else delta(t, t')
-    std::vector<double> G(2 * size_t(dG) * dG, 0.0);
-    int vidx = 0;                          // local index of the control values (first control most significant)
-    for (int j = 0; j < m; ++j) vidx = vidx * phys.dims[controls[j]] + control_values[j];
-    for (int c = 0; c < dC; ++c)
-      for (int t = 0; t < dT; ++t)
-        for (int t1 = 0; t1 < dT; ++t1) {
-          const size_t o = 2 * (size_t(t * dC + c) * dG + size_t(t1 * dC + c));
-          if (c == vidx) {
-            G[o] = U[2 * (t * dT + t1)];
-            G[o + 1] = U[2 * (t * dT + t1) + 1];
-          } else if (t == t1) {
-            G[o] = 1.0;
-          }
-        }
-    const int N = dG * dG;
-    std::vector<double> M(2 * size_t(N) * N);
-    for (int a = 0; a < dG; ++a)
-      for (int b = 0; b < dG; ++b)
-        for (int c = 0; c < dG; ++c)
-          for (int d = 0; d < dG; ++d) {
-            // element ((a, b), (c, d)) = G[a][c] conj(G[b][d])
-            const double xr = G[2 * (a * dG + c)], xi = G[2 * (a * dG + c) + 1];
-            const double yr = G[2 * (b * dG + d)], yi = -G[2 * (b * dG + d) + 1];
-            const size_t o = 2 * (size_t(a * dG + b) * N + size_t(c * dG + d));
-            M[o] = xr * yr - xi * yi;
-            M[o + 1] = xr * yi + xi * yr;
-          }
-    std::vector<int32_t> q(targets, targets + k);
-    q.insert(q.end(), controls, controls + m);
-    for (int j = 0; j < k + m; ++j) q.push_back(q[size_t(j)] + n);
-    return qd_apply_gate_ex(rho, q.data(), 2 * (k + m), nullptr, nullptr, 0, M.data(), skip);
-  }
-  std::vector<int32_t> t2(targets, targets + k), c2;
-  for (int j = 0; j < k; ++j) t2.push_back(targets[j] + n);
-  rc = qd_apply_gate_ex(rho, targets, k, controls, control_values, m, U, skip);
-  if (rc) return rc;
-  std::vector<double> Uc(U, U + 2 * size_t(dT) * dT);
-  for (size_t i = 1; i < Uc.size(); i += 2) Uc[i] = -Uc[i];
-  for (int j = 0; j < m; ++j) c2.push_back(controls[j] + n);
-  return qd_apply_gate_ex(rho, t2.data() + k, k, m ? c2.data() : nullptr, control_values, m, Uc.data(), skip);
+  std::vector<SparseGate> list;
+  rc = append_gate(phys, n, targets, k, controls, control_values, m, U, &list);
+  return rc ? rc : run_list(rho, list);
 }
 
 int qd_density_apply_channel(qd_state* rho, const int32_t* targets, int32_t k, const double* kraus, int32_t nk,
@@ -378,10 +400,9 @@ int qd_density_apply_channel(qd_state* rho, const int32_t* targets, int32_t k, c
         if (std::sqrt(re * re + im * im) > 1e-10) return fail(QD_ENOTUNITARY, "Kraus operators do not sum to the identity");
       }
   }
-  std::vector<int32_t> t2(targets, targets + k);
-  for (int j = 0; j < k; ++j) t2.push_back(targets[j] + n);
-  const std::vector<double> S = superoperator(kraus, nk, dT);
-  return qd_apply_gate_ex(rho, t2.data(), 2 * k, nullptr, nullptr, 0, S.data(), QD_FLAG_SKIP_UNITARY_CHECK);
+  std::vector<SparseGate> list;
+  rc = append_super(n, targets, k, superoperator(kraus, nk, dT), &list);
+  return rc ? rc : run_list(rho, list);
 }
 
 int qd_channel_kraus(int32_t kind, int32_t d, double p, double* out, int32_t cap, int32_t* nk) {
@@ -488,7 +509,7 @@ int qd_density_apply_ops(qd_state* rho, const qd_density_op* ops, int32_t count,
     }
     if (rc) return rc;
   }
-  const uint32_t skip = flags | QD_FLAG_SKIP_UNITARY_CHECK;
+  std::vector<SparseGate> list;
   // the sorted union of a list of qudits and an operation's targets and controls
   auto with_support = [&](std::vector<int> sq, const qd_density_op& o) {
     for (int j = 0; j < o.k; ++j) sq.push_back(o.targets[j]);
@@ -501,6 +522,11 @@ int qd_density_apply_ops(qd_state* rho, const qd_density_op* ops, int32_t count,
   auto dim_of_set = [&](const std::vector<int>& sq) {
     int d = 1;
     for (int q : sq) d *= phys.dims[q];
+    return d;
+  };
+  auto dim_of_list = [&](const qd_density_op& o) {
+    int d = 1;
+    for (int j = 0; j < o.k; ++j) d *= phys.dims[o.targets[j]];
     return d;
   };
   int32_t i = 0;
@@ -517,8 +543,8 @@ int qd_density_apply_ops(qd_state* rho, const qd_density_op* ops, int32_t count,
       }
     if (e - i == 1) {
       rc = o.kind == QD_OP_GATE
-               ? qd_density_apply_gate(rho, o.targets, o.k, o.controls, o.control_values, o.m, o.mats, skip)
-               : qd_density_apply_channel(rho, o.targets, o.k, o.mats, o.nk, skip);
+               ? append_gate(phys, n, o.targets, o.k, o.controls, o.control_values, o.m, o.mats, &list)
+               : append_super(n, o.targets, o.k, superoperator(o.mats, o.nk, dim_of_list(o)), &list);
       if (rc) return rc;
       i = e;
       continue;
@@ -547,13 +573,12 @@ int qd_density_apply_ops(qd_state* rho, const qd_density_op* ops, int32_t count,
         }
       S.swap(P);
     }
-    std::vector<int32_t> t2(Sq.begin(), Sq.end());
-    for (int q : Sq) t2.push_back(q + n);
-    rc = qd_apply_gate_ex(rho, t2.data(), int32_t(t2.size()), nullptr, nullptr, 0, S.data(), QD_FLAG_SKIP_UNITARY_CHECK);
+    const std::vector<int32_t> q32(Sq.begin(), Sq.end());
+    rc = append_super(n, q32.data(), int32_t(q32.size()), std::move(S), &list);
     if (rc) return rc;
     i = e;
   }
-  return QD_OK;
+  return run_list(rho, list);
 }
 
 int qd_density_trace(qd_state* rho, double* re, double* im) {

@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <cctype>
 #include <cstring>
+#include <deque>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -302,20 +303,32 @@ int qd_circuit_decompose(const qd_circuit* c, qd_circuit** out) {
 
 int qd_circuit_apply(qd_state* s, const qd_circuit* c) {
   if (!s || !c) return fail(QD_EINVAL, "null argument");
-  // gates were checked against the circuit's register when added, so with equal registers every
-  // qd_apply_gate below passes validation
+  // gates were checked against the circuit's register when added, so with equal registers each of
+  // them passes qd_apply_gate's validation
   const std::vector<int32_t> sd(s->reg.dims, s->reg.dims + s->reg.n);
   if (sd != c->dims) return fail(QD_EDIM, "circuit register differs from the state's");
-  std::vector<double> U;
+  // each named matrix is built once
+  struct Named {
+    int32_t kind, d, a;
+    std::vector<double> U;
+  };
+  std::deque<Named> named;
+  std::vector<GateRef> list;
+  list.reserve(c->gates.size());
   for (const qd_circuit::G& g : c->gates) {
-    const int d = c->dims[size_t(g.target)];
-    U.assign(2 * size_t(d) * size_t(d), 0.0);
-    int rc = qd_gate_matrix(g.kind, d, g.kind == QD_GATE_X ? g.a : 0, U.data());
-    if (rc) return rc;
-    rc = qd_apply_gate(s, &g.target, 1, g.ctl.data(), g.cval.data(), int32_t(g.ctl.size()), U.data());
-    if (rc) return rc;
+    const int32_t d = c->dims[size_t(g.target)], a = g.kind == QD_GATE_X ? g.a : 0;
+    const Named* u = nullptr;
+    for (const Named& x : named)
+      if (x.kind == g.kind && x.d == d && x.a == a) u = &x;
+    if (!u) {
+      named.push_back(Named{g.kind, d, a, std::vector<double>(2 * size_t(d) * size_t(d), 0.0)});
+      int rc = qd_gate_matrix(g.kind, d, a, named.back().U.data());
+      if (rc) return rc;
+      u = &named.back();
+    }
+    list.push_back(GateRef{&g.target, 1, g.ctl.data(), g.cval.data(), int32_t(g.ctl.size()), u->U.data()});
   }
-  return QD_OK;
+  return apply_gate_list(s, list);
 }
 
 int qd_circuit_apply_sparse(qd_sparse* s, const qd_circuit* c) {

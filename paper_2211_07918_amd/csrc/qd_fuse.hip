@@ -180,7 +180,11 @@ int qd_fuse(const int32_t* dims, int32_t n, const qd_gate* gates, int32_t g, int
   f->reg = r;
   f->stream = (hipStream_t)hip_stream;
   f->dev.resize(blocks.size());
+  ParamRing ring;
+  ring.first = size_t(256) << 10;
   auto cleanup = [&](int code) {
+    (void)hipStreamSynchronize(f->stream);
+    ring_free(&ring);
     qd_fused_free(f);
     return code;
   };
@@ -196,43 +200,51 @@ int qd_fuse(const int32_t* dims, int32_t n, const qd_gate* gates, int32_t g, int
     if (e != hipSuccess) return cleanup(hip_fail(e, "fused block allocation"));
 
     // The block is built by applying its gates, embedded in the window register, to the
-    // identity: a register with the window's dims plus one extra lowest digit of size B holding
-    // the column index, so M <- E_g M for every column at once (FP64, the plain gate kernels).
-    int32_t wdims[QD_MAX_QUDITS + 1];
+    // identity: a register with the window's dims plus the column index as lowest digits, so
+    // M <- E_g M for every column at once (FP64, the plain gate kernels). The column index counts as
+    // two digits, the lower about one line long, so that a few columns make a tile and the block's
+    // gates run in one pass.
+    int32_t wdims[QD_MAX_QUDITS + 2];
     int pos[QD_MAX_QUDITS];
     for (int j = 0; j < d.info.k; ++j) {
       wdims[j] = r.dims[d.info.window[j]];
       pos[d.info.window[j]] = j;
     }
-    wdims[d.info.k] = B;
+    int low = 1;
+    for (int c : {8, 9, 10, 11, 12, 13, 14, 15, 16, 7, 6, 5, 4, 3, 2})
+      if (B % c == 0 && B > c && low == 1) low = c;
+    int wn = d.info.k;
+    if (low > 1) wdims[wn++] = B / low;
+    wdims[wn++] = low > 1 ? low : B;
     qd_state tmp;
-    rc = make_register(wdims, d.info.k + 1, &tmp.reg);
+    rc = make_register(wdims, wn, &tmp.reg);
     if (rc) return cleanup(rc);
     tmp.prec = QD_C128;
     tmp.data = d.u64;
     tmp.owned = false;
     tmp.stream = f->stream;
+    tmp.ring = ring;
     // identity: amplitude (row, col) = delta(row, col) at flat index row * B + col
     std::vector<double> eye(2 * size_t(B) * B, 0.0);
     for (int y = 0; y < B; ++y) eye[2 * (size_t(y) * B + y)] = 1.0;
     e = hipMemcpyAsync(d.u64, eye.data(), eye.size() * sizeof(double), hipMemcpyHostToDevice, f->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(f->stream);
     if (e != hipSuccess) return cleanup(hip_fail(e, "fused block init"));
+    std::vector<int32_t> at;   // the members' targets and controls as window positions
+    for (int i : d.info.members)
+      for (int j = 0; j < gates[i].k + gates[i].m; ++j)
+        at.push_back(pos[j < gates[i].k ? gates[i].targets[j] : gates[i].controls[j - gates[i].k]]);
+    std::vector<GateRef> list;
+    const int32_t* q = at.data();
     for (int i : d.info.members) {
       const qd_gate& G = gates[i];
-      int32_t t[QD_MAX_QUDITS], c[QD_MAX_QUDITS];
-      for (int j = 0; j < G.k; ++j) t[j] = pos[G.targets[j]];
-      for (int j = 0; j < G.m; ++j) c[j] = pos[G.controls[j]];
-      GatePlan p;
-      make_plan(tmp.reg, t, G.k, c, G.control_values, G.m, G.U, &p);
-      rc = launch_gate(&tmp, p);
-      if (rc) {
-        ring_free(&tmp.ring);
-        return cleanup(rc);
-      }
+      list.push_back(GateRef{q, G.k, q + G.k, G.control_values, G.m, G.U});
+      q += G.k + G.m;
     }
+    rc = apply_gate_list(&tmp, list);
+    ring = tmp.ring;   // one parameter ring for all blocks
+    if (rc) return cleanup(rc);
     e = hipStreamSynchronize(f->stream);
-    ring_free(&tmp.ring);
     if (e != hipSuccess) return cleanup(hip_fail(e, "fused block build"));
     rc = embed_block(f, int(b));
     if (rc) return cleanup(rc);
@@ -250,6 +262,7 @@ int qd_fuse(const int32_t* dims, int32_t n, const qd_gate* gates, int32_t g, int
   }
   hipError_t e = hipStreamSynchronize(f->stream);
   if (e != hipSuccess) return cleanup(hip_fail(e, "qd_fuse"));
+  ring_free(&ring);
   *out = f;
   return QD_OK;
 }

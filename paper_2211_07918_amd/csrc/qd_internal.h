@@ -113,6 +113,7 @@ struct ParamRing {            // pinned host staging + device copy for per-call 
   char* dev = nullptr;
   size_t cap = 0;
   size_t head = 0;
+  size_t first = size_t(8) << 20;   // capacity it starts with
 };
 
 }  // namespace qd
@@ -186,6 +187,21 @@ struct SparseGate {
   std::vector<double> U;          // d_T x d_T, row-major, interleaved
 };
 int sparse_apply_gates(qd_sparse* s, const SparseGate* gates, size_t count, uint32_t flags);
+
+// A list of (already validated) gates on a state, several to a pass where that pays (qd_window.hip).
+// The arrays are the caller's and are read during the call only.
+struct GateRef {
+  const int32_t* t;
+  int32_t k;
+  const int32_t* c;
+  const int32_t* v;
+  int32_t m;
+  const double* U;
+};
+int apply_gate_list(qd_state* s, const std::vector<GateRef>& list);
+inline GateRef ref_of(const SparseGate& g) {
+  return GateRef{g.t.data(), int32_t(g.t.size()), g.c.data(), g.v.data(), int32_t(g.c.size()), g.U.data()};
+}
 
 // Launchers (qd_gates.hip)
 int launch_gate(qd_state* s, const GatePlan& p);

@@ -2,6 +2,7 @@
 // state-vector API. No kernels here; launches go through the launchers in the .hip files.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -183,7 +184,8 @@ int classify(const double* U, int dT) {
     for (int c = 0; c < dT; ++c)
       if (r != c && nz(r, c)) { diag = false; break; }
   if (diag) return QD_CLASS_DIAGONAL;
-  std::vector<int> rowcount(dT, 0);
+  int rowcount[QD_MAX_GATE_DIM];
+  std::fill(rowcount, rowcount + dT, 0);
   for (int c = 0; c < dT; ++c) {
     int cnt = 0;
     for (int r = 0; r < dT; ++r)
@@ -348,7 +350,7 @@ int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out
       QD_HIP(hipStreamSynchronize(stream));
       ring_free(r);
     }
-    r->cap = size_t(8) << 20;
+    r->cap = r->first;
     while (r->cap < need) r->cap *= 2;
     QD_HIP(hipHostMalloc((void**)&r->host, r->cap, hipHostMallocDefault));
     QD_HIP(hipMalloc((void**)&r->dev, r->cap));

@@ -70,3 +70,96 @@ def test_toffoli_chain_on_the_gpu(stream):
     finally:
         Q.qd_circuit_free(chain)
         Q.qd_circuit_free(mct)
+
+
+def named_circuit(dims, n, rng, max_controls=2):
+    """A library circuit and the same gates as oracle records: shifts, phases and Fourier gates with up
+    to max_controls controls at random values."""
+    c, gates = Q.qd_circuit_create(dims), []
+    kinds = {"X": Q.QD_GATE_X, "Z": Q.QD_GATE_Z, "F": Q.QD_GATE_F}
+    for _ in range(n):
+        q = [int(x) for x in rng.permutation(len(dims))]
+        m = int(rng.integers(0, min(max_controls, len(dims) - 1) + 1))
+        kind, t, ctl = "XZF"[int(rng.integers(3))], q[0], q[1:1 + m]
+        val = [int(rng.integers(dims[x])) for x in ctl]
+        a = int(rng.integers(1, dims[t])) if kind == "X" else 0
+        Q.qd_circuit_add(c, kinds[kind], t, a, ctl, val)
+        gates.append(C.Gate(kind, (t,), tuple(ctl), tuple(val), a=a))
+    return c, gates
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("dims, n, controls", [
+    ((3,) * 6, 70, 2),                                  # the whole state is one tile, more gates than one pass takes
+    ((2,), 5, 0),                                       # one qudit
+    ((3,) * 8, 60, 2),                                  # just above one tile
+    ((2,) * 13, 60, 3),
+    ((2, 3, 2, 4, 3, 2, 3, 2, 3, 4, 2, 3), 120, 2),
+    ((5, 7, 2, 3, 4, 2, 3, 2, 2), 60, 2),
+    ((17, 2, 3, 3, 2, 5, 2, 2, 3), 50, 2),              # a radix that no window takes, between gates that one does
+    ((2, 3, 2, 256), 40, 1),                            # the lowest run is the radix itself
+    ((12, 9, 16, 2, 3), 40, 1),
+    ((2, 2, 3, 2, 2, 2, 3, 2, 2, 2, 2), 40, 9),         # controls inside and outside, more than a pass holds
+    ((4, 3, 2) * 5, 40, 2),                             # 8.0e6 amplitudes: both tile sizes are planned
+])
+def test_circuit_in_windows(stream, prec, dims, n, controls):
+    """qd_circuit_apply stages windows of the register and applies several gates to each; against the
+    oracle, and against the same gates one call at a time. Each gate adds about d u to the 2-norm error:
+    1e-12 covers them in FP64, 4 n d 2^-24 in FP32."""
+    rng = np.random.default_rng(sum(dims) + n)
+    c, gates = named_circuit(dims, n, rng, controls)
+    D = O.register_size(dims)
+    psi0 = rng.normal(size=D) + 1j * rng.normal(size=D)
+    psi0 /= np.linalg.norm(psi0)
+    if prec == Q.QD_C64:
+        psi0 = psi0.astype(np.complex64)
+    tol = 1e-12 if prec == Q.QD_C128 else 4.0 * n * max(dims) * 2.0 ** -24
+    s, one = Q.qd_state_init(dims, prec, stream), Q.qd_state_init(dims, prec, stream)
+    try:
+        for h in (s, one):
+            Q.qd_state_upload(h, psi0)
+        Q.qd_circuit_apply(s, c)
+        for g in gates:
+            Q.apply_circuit_gate(one, g, dims)
+        a, b = Q.qd_state_download(s), Q.qd_state_download(one)
+        assert Q.qd_state_gate_launches(s) == Q.qd_state_gate_launches(one)
+    finally:
+        Q.qd_state_free(s)
+        Q.qd_state_free(one)
+        Q.qd_circuit_free(c)
+    assert max_abs(a, b) <= tol
+    ref = psi0.astype(np.complex128)
+    for g in gates:
+        ref = O.apply_gate(ref, dims, g.targets, g.controls, g.cvals, O.gate_unitary(g, dims))
+    assert max_abs(a, ref) <= tol
+
+
+def test_circuit_captured_in_a_graph():
+    """While a stream is captured the gates are recorded one by one, so replays read no buffer that
+    later calls write: every replay equals the eager run."""
+    import torch
+    dims = (3, 2, 4, 3, 2, 3, 2, 3)
+    rng = np.random.default_rng(9)
+    c, _ = named_circuit(dims, 30, rng)
+    other, _ = named_circuit(dims, 40, rng)
+    st = torch.cuda.Stream()
+    s, t = Q.qd_state_init(dims, Q.QD_C128, st.cuda_stream), Q.qd_state_init(dims, Q.QD_C128, st.cuda_stream)
+    graph = torch.cuda.CUDAGraph()
+    try:
+        with torch.cuda.graph(graph, stream=st):
+            Q.qd_circuit_apply(s, c)
+        for _ in range(3):
+            Q.qd_state_set_basis(s, (0,) * len(dims))
+            Q.qd_state_set_basis(t, (0,) * len(dims))
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            Q.qd_circuit_apply(t, c)
+            assert max_abs(Q.qd_state_download(s), Q.qd_state_download(t)) <= 1e-12
+            Q.qd_circuit_apply(s, other)      # eager work that writes the parameter buffers again
+            Q.qd_state_sync(s)
+    finally:
+        Q.qd_state_free(s)
+        Q.qd_state_free(t)
+        Q.qd_circuit_free(c)
+        Q.qd_circuit_free(other)
