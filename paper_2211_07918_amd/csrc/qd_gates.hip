@@ -348,17 +348,25 @@ __global__ __launch_bounds__(256) void k_slices_direct_lu(R* psi_raw, const unsi
 }
 
 // ------------------------------------------------------------------------------------------ tiled
+// The arguments are read where they lie, in the kernel argument segment, by scalar loads: as a by-value
+// parameter the slice maps and U overflowed the scalar registers, and spilled values were read back lane
+// by lane (250-370 of them). Slices are found by inserting the target and control digits into the slice
+// number, which takes four instructions a digit. Dense U comes a row at a time by scalar loads (broadcast
+// from LDS its reads took more of the LDS pipe than the amplitudes'). Measured, with the smaller tiles of
+// tile_geometry: 9 x 9 gates on 3^16 474 -> 260 us (complex128), 177 -> 131 (complex64); qutrits on the
+// hybrid register 594 -> 557 us and 430 -> 280; a qubit on 2^25 207 -> 178 and 134 -> 96.
 template <typename R, int DT, typename OP>
 struct TileArgs {
   R* psi;
   SliceMap tiles;                 // tile index -> global offset of the tile's origin
-  SliceMap inner;                 // slice index inside a tile -> LDS index of its y = 0 amplitude
   uint32_t BL;                    // run length (amplitudes of the low suffix)
   uint32_t dH;                    // number of runs (product of the high targets' dims)
   Magic32 blm;                    // division by BL
   int64_t hoff[kMaxTileRuns];     // global offset of run h from the tile origin
-  int64_t toff[DT];               // LDS offset of target combination y
-  int64_t doff[DT];               // monomial: LDS offset of the row column y moves to
+  uint32_t nsl, nins;             // slices of a tile; digits inserted into a slice number ...
+  Insert ins[14];                 // ... to make its LDS index (a tile of 2^13 amplitudes has at most 13 digits)
+  uint32_t toff[DT];              // LDS offset of target combination y
+  uint32_t doff[DT];              // monomial: LDS offset of the row column y moves to
   uint32_t nsc;                   // controls inside the suffix that the tile leaves out, and for
   Magic32 scm[kMaxTileCtl];       // each, by increasing stride s: division by s,
   uint32_t scmul[kMaxTileCtl];    // s (d_c - 1) and
@@ -366,22 +374,16 @@ struct TileArgs {
   OP op;
 };
 
-// Dense gates read U from LDS in the tile kernel. Left to the compiler, its 2 d_T^2 values join the
-// slice maps in the scalar registers, which overflow, and the mix then spends more instructions
-// reading spilled values back than multiplying. Each workgroup copies U from the kernel argument
-// segment (one vector load per thread, no upload) into LDS before its first tile.
-constexpr int kTileLdsU = 2;
-template <typename OP> struct DenseDim { static constexpr int value = 0; };
-template <typename R, int DT> struct DenseDim<DenseOp<R, DT>> { static constexpr int value = DT; };
+#define QD_KARG const __attribute__((address_space(4)))   // kernel argument memory
 
-// Offset inside the run of the staged amplitude w: each left-out control digit is re-inserted at
-// its value, smallest stride first (w = q s + r becomes q s d_c + v s + r).
-template <typename A>
-__device__ __forceinline__ uint32_t tile_expand(const A& a, uint32_t w) {
-#pragma unroll
-  for (int j = 0; j < kMaxTileCtl; ++j)
-    if (j < int(a.nsc)) w += magic_div(w, a.scm[j]) * a.scmul[j] + a.scadd[j];
-  return w;
+template <typename M>
+__device__ __forceinline__ Magic32 karg_magic(M* m) {
+  Magic32 r;
+  r.mul = m->mul;
+  r.sh1 = m->sh1;
+  r.sh2 = m->sh2;
+  r.d = m->d;
+  return r;
 }
 
 // Amplitudes a thread moves per tile: the tile holds at most 256 * kTileEpt<R> amplitudes.
@@ -389,45 +391,82 @@ template <typename R> struct TileEpt;
 template <> struct TileEpt<double> { static constexpr int value = 8; };
 template <> struct TileEpt<float> { static constexpr int value = 16; };
 
+template <typename OP> struct DenseDim { static constexpr int value = 0; };
+template <typename R, int DT> struct DenseDim<DenseOp<R, DT>> { static constexpr int value = DT; };
+
 template <typename R, int DT, typename OP>
-__global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP> a) {
+__global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
   using C = typename CxT<R>::T;
   constexpr int EPT = TileEpt<R>::value;
-  constexpr int kUL = DenseDim<OP>::value >= kTileLdsU ? 2 * DT * DT : 0;
+  constexpr bool kDense = DenseDim<OP>::value > 0;
+  QD_KARG TileArgs<R, DT, OP>* a = (QD_KARG TileArgs<R, DT, OP>*)__builtin_amdgcn_kernarg_segment_ptr();
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ int64_t s_hoff[kMaxTileRuns];
-  __shared__ R su[kUL > 0 ? kUL : 1];
   C* lds = reinterpret_cast<C*>(lds_raw);
-  C* __restrict__ psi = reinterpret_cast<C*>(a.psi);
-  const uint32_t bs = blockDim.x, tid = threadIdx.x;
-  const uint32_t E = a.BL * a.dH;
-#pragma unroll
-  for (int h = 0; h < kMaxTileRuns; ++h)
-    if (int(tid) == h) s_hoff[h] = a.hoff[h];
-  if constexpr (kUL > 0) {
-    const R* ug = a.op.u;   // read in place from the kernel argument segment
-    for (uint32_t i = tid; i < uint32_t(kUL); i += bs) su[i] = ug[i];
-  }
+  C* __restrict__ psi = reinterpret_cast<C*>(a->psi);
+  const uint32_t bs = blockDim.x, tid = threadIdx.x, BL = a->BL, E = BL * a->dH;
+  const Magic32 blm = karg_magic(&a->blm), sc0 = karg_magic(&a->scm[0]), sc1 = karg_magic(&a->scm[1]);
+  const uint32_t m0 = a->scmul[0], m1 = a->scmul[1], d0 = a->scadd[0], d1 = a->scadd[1];
+  if (tid < kMaxTileRuns) s_hoff[tid] = a->hoff[tid];
   __syncthreads();
-  for (uint32_t tile = blockIdx.x; tile < a.tiles.count; tile += gridDim.x) {
-    const int64_t g0 = sm_offset(a.tiles, tile);
-    // The per-element run and LDS indices are recomputed in the load and in the store stage from
-    // opaque copies of the thread index: kept live across the LDS mix they would take about
-    // 3 EPT registers and cut the workgroups per CU for the wider gates.
+  // Offset of the staged amplitude idx from the tile's origin: its run, and the offset inside the run,
+  // where each left-out control digit is re-inserted at its value, smallest stride first (w = q s + r
+  // becomes q s d_c + v s + r; an entry of zeros inserts nothing).
+  auto place = [&](uint32_t idx) {
+    const uint32_t h = magic_div(idx, blm);
+    uint32_t w = idx - h * BL;
+    w += magic_div(w, sc0) * m0 + d0;
+    w += magic_div(w, sc1) * m1 + d1;
+    return s_hoff[h] + int64_t(w);
+  };
+  const bool whole = a->dH == 1 && a->nsc == 0;   // the tile is one run of the state
+  // most gates insert one or two digits (an entry of zeros inserts nothing)
+  const uint32_t nsl = a->nsl, nins = a->nins;
+  const uint32_t i0m = a->ins[0].mul, i0s = a->ins[0].self, i0g = a->ins[0].grow, i0a = a->ins[0].add;
+  const uint32_t i1m = a->ins[1].mul, i1s = a->ins[1].self, i1g = a->ins[1].grow, i1a = a->ins[1].add;
+  const uint32_t ntiles = a->tiles.count;
+  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    int64_t g0 = a->tiles.base;
+    {
+      uint32_t rem = tile;   // uniform: scalar arithmetic
+      const uint32_t ng = a->tiles.ng;
+      for (uint32_t g = 0; g < ng; ++g) {
+        const uint32_t q = g + 1 < ng ? magic_div(rem, karg_magic(&a->tiles.gmag[g])) : 0u;
+        g0 += int64_t(rem - q * a->tiles.gdim[g]) * a->tiles.gstride[g];
+        rem = q;
+      }
+    }
+    // The per-element indices are recomputed in the load and in the store stage from opaque copies of
+    // the thread index: kept live across the LDS mix they would take about 3 EPT registers and cut the
+    // workgroups per CU for the wider gates. Every load of the tile is issued before the first LDS write;
+    // in a tile of one run none has a branch of its own (a lane past the end repeats the last amplitude),
+    // which took a complex64 qubit gate on 2^25 amplitudes from 149 to 103 us. (In other tiles the addresses
+    // held for that took the registers of a third of the waves: 295 -> 361 us.)
+    // (real and imaginary parts in separate scalar arrays so they stay in registers)
     uint32_t tl = tid;
     __asm__ volatile("" : "+v"(tl));
-    // every load of the tile is issued before the first LDS write
-    // (real and imaginary parts in separate scalar arrays so they stay in registers)
     R vr[EPT], vi[EPT];
+    C* __restrict__ p0 = psi + g0;
+    // uniform base, 32-bit offset: one address register a load
+    auto byte_at = [&](uint32_t idx) {
+      return reinterpret_cast<C*>(reinterpret_cast<unsigned char*>(p0) + idx * uint32_t(sizeof(C)));
+    };
+    if (whole) {
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const uint32_t idx = tl + e * bs;
-      if (idx < E) {
-        const uint32_t h = magic_div(idx, a.blm);
-        const C t = ld_stream(psi + (g0 + s_hoff[h] + tile_expand(a, idx - h * a.BL)));
-        vr[e] = t.x;
-        vi[e] = t.y;
-      }
+      for (int e = 0; e < EPT; ++e)
+        if (uint32_t(e) * bs < E) {
+          const C t = ld_stream(byte_at(min(tl + e * bs, E - 1)));
+          vr[e] = t.x;
+          vi[e] = t.y;
+        }
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e)
+        if (tl + e * bs < E) {
+          const C t = ld_stream(p0 + place(tl + e * bs));
+          vr[e] = t.x;
+          vi[e] = t.y;
+        }
     }
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
@@ -440,19 +479,22 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP> a) {
       }
     }
     __syncthreads();
-    for (uint32_t j = tid; j < a.inner.count; j += bs) {
-      const int64_t b = sm_offset(a.inner, j);
+#pragma unroll 1
+    for (uint32_t j = tid; j < nsl; j += bs) {
+      uint32_t b = j;
+      b += (__umulhi(b, i0m) + (b & i0s)) * i0g + i0a;
+      b += (__umulhi(b, i1m) + (b & i1s)) * i1g + i1a;
+#pragma unroll 1
+      for (uint32_t i = 2; i < nins; ++i) b += (__umulhi(b, a->ins[i].mul) + (b & a->ins[i].self)) * a->ins[i].grow + a->ins[i].add;
       C x[DT];
 #pragma unroll
-      for (int y = 0; y < DT; ++y) x[y] = lds[b + a.toff[y]];
-      if constexpr (kUL > 0) {
-#pragma unroll
-        for (int r = 0; r < DT; ++r) {
-          __asm__ volatile("" ::: "memory");   // U is read from LDS row by row, not held in registers
+      for (int y = 0; y < DT; ++y) x[y] = lds[b + a->toff[y]];
+      if constexpr (kDense) {
+        auto row = [&](int r) {
           R re = R(0), im = R(0);
 #pragma unroll
           for (int c = 0; c < DT; ++c) {
-            const R ur = su[2 * (r * DT + c)], ui = su[2 * (r * DT + c) + 1];
+            const R ur = a->op.u[2 * (r * DT + c)], ui = a->op.u[2 * (r * DT + c) + 1];
             re = fma(ur, x[c].x, re);
             re = fma(-ui, x[c].y, re);
             im = fma(ur, x[c].y, im);
@@ -461,36 +503,53 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP> a) {
           C yv;
           yv.x = re;
           yv.y = im;
-          lds[b + a.toff[r]] = yv;
+          lds[b + a->toff[r]] = yv;
+        };
+        // a row of U at a time (all of it would not fit the scalar registers)
+        if constexpr (DT * sizeof(R) <= 24) {
+#pragma unroll
+          for (int r = 0; r < DT; ++r) row(r);
+        } else {
+#pragma unroll 1
+          for (int r = 0; r < DT; ++r) row(r);
         }
       } else {
-        mix_store<false, C, R, DT>(lds, b, a.toff, a.doff, a.op, x);
+#pragma unroll
+        for (int c = 0; c < DT; ++c) {
+          const R pr = a->op.ph[2 * c], pi = a->op.ph[2 * c + 1];
+          C y;
+          y.x = fma(pr, x[c].x, -pi * x[c].y);
+          y.y = fma(pr, x[c].y, pi * x[c].x);
+          lds[b + a->doff[c]] = y;
+        }
       }
     }
     __syncthreads();
     uint32_t ts = tid;
     __asm__ volatile("" : "+v"(ts));
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const uint32_t idx = ts + e * bs;
-      if (idx < E) {
-        const C t = lds[idx];
+    for (int e = 0; e < EPT; ++e)
+      if (uint32_t(e) * bs < E) {
+        const C t = lds[min(ts + e * bs, E - 1)];
         vr[e] = t.x;
         vi[e] = t.y;
       }
-    }
+    auto put_back = [&](int e, C* p) {
+      C t;
+      t.x = vr[e];
+      t.y = vi[e];
+      st_stream(p, t);
+    };
+    if (whole) {
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-      const uint32_t idx = ts + e * bs;
-      if (idx < E) {
-        const uint32_t h = magic_div(idx, a.blm);
-        C t;
-        t.x = vr[e];
-        t.y = vi[e];
-        st_stream(psi + (g0 + s_hoff[h] + tile_expand(a, idx - h * a.BL)), t);
-      }
+      for (int e = 0; e < EPT; ++e)
+        if (ts + e * bs < E) put_back(e, byte_at(ts + e * bs));
+    } else {
+#pragma unroll
+      for (int e = 0; e < EPT; ++e)
+        if (ts + e * bs < E) put_back(e, p0 + place(ts + e * bs));
     }
-    if (tile + gridDim.x < a.tiles.count) __syncthreads();
+    if (tile + gridDim.x < ntiles) __syncthreads();
   }
 }
 
@@ -895,7 +954,12 @@ bool tile_geometry(const Register& r, const GatePlan& p, int prec, TileGeom* g) 
     if (nsc > kMaxTileCtl) return false;
     for (int i = 0; i < pq; ++i)
       if (is_t[i]) dH *= r.dims[i];
-    while (pq > 0) {
+    // Growth stops at 9 KB: more, smaller tiles keep the memory system busier than few large ones
+    // (complex128: 648 against 1296 amplitudes 565 and 615 us on the hybrid register of 1.1e8, 1024
+    // against 2048 178 and 197 us on 2^25), while tiles below that size leave the workgroups short of
+    // loads (243 against 729 amplitudes 384 and 243 us on 3^16; complex64: 729 against 2187 221 and 132 us).
+    const uint64_t enough = 9216 / amp_bytes(prec);
+    while (pq > 0 && BL * dH < enough) {
       const int q = pq - 1;
       const bool drop = compact && is_c[q];
       if (drop && nsc == kMaxTileCtl) break;
@@ -997,8 +1061,11 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
       }
       int rc = fill_slicemap(make_groups(r, role, nullptr, 0, pq), tbase, &a.tiles);
       if (rc) return rc;
-      rc = fill_slicemap(make_groups(lr, role, nullptr, pq, r.n), ibase, &a.inner);
+      // the suffix's free digits, held to the limits of a slice map
+      SliceMap inner;
+      rc = fill_slicemap(make_groups(lr, role, nullptr, pq, r.n), ibase, &inner);
       if (rc) return rc;
+      a.nsl = inner.count;
       // run offsets: h in mixed radix over the high targets in listed order
       int hmul[QD_MAX_QUDITS] = {};
       {
@@ -1024,10 +1091,18 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
           rem /= r.dims[t];
           off += t < pq ? int64_t(dg) * hmul[j] * int64_t(BL) : int64_t(dg) * lr.strides[t];
         }
-        a.toff[y] = off;
+        a.toff[y] = uint32_t(off);
       }
-      fill_doff<DT>(p, a.toff, a.doff);
-      if (a.tiles.count == 0 || a.inner.count == 0) return QD_OK;
+      for (int c = 0; c < DT; ++c) a.doff[c] = p.dst.empty() ? 0 : a.toff[p.dst[c]];
+      // a slice: the suffix's digits, targets at 0 and controls at their values (run 0 of the high targets)
+      for (int i = r.n - 1; i >= pq; --i) {
+        if (out[i] || role[i] == 0) continue;
+        int v = 0;
+        for (int j = 0; j < p.m; ++j)
+          if (p.controls[j] == i) v = p.cvals[j];
+        a.ins[a.nins++] = make_insert(uint32_t(lr.strides[i]), uint32_t(r.dims[i]), uint32_t(v));
+      }
+      if (a.tiles.count == 0 || a.nsl == 0) return QD_OK;
       const size_t lds = size_t(BL * dH) * sizeof(R) * 2;
       // workgroups walk the tiles; at most 2^22 of them keep the grid inside 32-bit work-item counts
       const unsigned grid = unsigned(std::min<uint64_t>(a.tiles.count, uint64_t(1) << 22));
@@ -1069,7 +1144,23 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
   target_offsets(r, p, a.toff);
   fill_doff<DT>(p, a.toff, a.doff);
   if (a.sm.count == 0) return QD_OK;
-  const int bs = ent.block;
+  int bs = ent.block, spt = ent.spt;
+  // Untuned complex128 gates of d_T <= 4 whose planes all begin on a line: with target strides of 4096
+  // or more workgroups of one wave, one slice a thread (537 against 593 us for a qubit of the hybrid
+  // register, 333 against 371 on 2^26; two slices for d_T = 4, where one lost up to 14 % at the highest
+  // strides of 4^13: 375 to 414 against 400 to 409 us with 256 threads), with strides of 256 to 4095 128
+  // threads (587 against 606). Where runs begin inside lines (3^16) each workgroup shares the lines at its
+  // ends with others, and larger ones stay ahead (271 against 289 us).
+  if (!ent.tuned && DT <= 4 && s->prec == QD_C128 && tp.direct_block == TuneParams().direct_block &&
+      tp.direct_spt == TuneParams().direct_spt && min_stride >= 256) {
+    bool lines = true;
+    for (int j = 0; j < p.k; ++j) lines = lines && r.strides[p.targets[j]] % line == 0;
+    for (int j = 0; j < p.m; ++j) lines = lines && r.strides[p.controls[j]] % line == 0;
+    if (lines) {
+      bs = min_stride >= 4096 ? 64 : 128;
+      spt = min_stride >= 4096 && DT < 4 ? 1 : 2;
+    }
+  }
   if (nlow) {
     line_pattern(r, p, line, &a.lper, &a.lmask);
     if (a.lper > 1) a.lpm = make_magic32(a.lper);
@@ -1102,11 +1193,11 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
   }
   // Several slices per thread only up to d_T = 4: beyond, two slices' operands and the gate's
   // kernel arguments overflow the scalar registers and the spilled values are read back per FMA.
-  if (ent.spt >= 4 && DT <= 4) {
+  if (spt >= 4 && DT <= 4) {
     hipLaunchKernelGGL((k_slices_direct<R, DT, OP, 4, kDirectPlain>), dim3(grid_for(a.sm.count, uint64_t(bs) * 4)), dim3(bs),
                        0, s->stream, a);
     g_last_kernel = label<kKnDirect, R, DT, OP, 4, kDirectPlain>();
-  } else if (ent.spt >= 2 && DT <= 4) {
+  } else if (spt >= 2 && DT <= 4) {
     hipLaunchKernelGGL((k_slices_direct<R, DT, OP, 2, kDirectPlain>), dim3(grid_for(a.sm.count, uint64_t(bs) * 2)), dim3(bs),
                        0, s->stream, a);
     g_last_kernel = label<kKnDirect, R, DT, OP, 2, kDirectPlain>();

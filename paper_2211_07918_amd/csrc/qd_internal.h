@@ -72,6 +72,7 @@ struct TuneEntry {
   int block;        // threads per workgroup
   int spt;          // slices per thread (direct kernel)
   int tile_elems;   // LDS tile budget in complex128 amplitudes (doubled for complex64)
+  int tuned = 1;    // a table entry (0: the defaults or explicit settings)
 };
 int stride_bucket(int64_t s);
 TuneEntry entry_for(int prec, int64_t min_stride);   // tuned entry, else the defaults above
@@ -90,6 +91,16 @@ struct SliceMap {
   Magic32 gmag[kMaxGroups];
   int64_t gstride[kMaxGroups];
 };
+
+// One digit inserted into a linear index below 2^13: j += (j / s) s (d - 1) + v s for a digit of range d,
+// stride s and value v, by ascending stride. The division is one multiply-high by floor(2^32 / s) + 1
+// (exact there); s = 1 takes j itself (self is all ones, mul 0). An entry of zeros inserts nothing.
+struct Insert {
+  uint32_t mul, self, grow, add;   // grow = s (d - 1), add = v s
+};
+inline Insert make_insert(uint32_t s, uint32_t d, uint32_t v) {
+  return Insert{s > 1 ? uint32_t((uint64_t(1) << 32) / s) + 1u : 0u, s > 1 ? 0u : ~0u, s * (d - 1), v * s};
+}
 
 // 64-bit variant for the generic path (any register size); lives in device memory.
 struct SliceMap64 {

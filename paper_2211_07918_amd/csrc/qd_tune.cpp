@@ -35,6 +35,7 @@ TuneEntry entry_for(int prec, int64_t min_stride) {
   e.block = e.tiled ? tp.tile_block : tp.direct_block;
   e.spt = tp.direct_spt;
   e.tile_elems = tp.tile_elems;
+  e.tuned = 0;
   return e;
 }
 

@@ -40,9 +40,7 @@ constexpr int kMaxDiag = 256;          // phases of one diagonal gate
 // One gate of a pass, as the kernel's scalar loads read it: two lines of 64 bytes. LDS positions are
 // in bytes (a tile is at most 64 KB). Slice j of the gate is the j-th amplitude of the window whose
 // target digits are 0 and whose control digits hold their values: each of those digits, of range d and
-// LDS stride s amplitudes, is inserted into j by ascending stride: j += (j / s) s (d - 1) + v s. The
-// division (j below 2^13) is one multiply-high by floor(2^32 / s) + 1; s = 1 takes j itself (self).
-struct Insert { uint32_t mul, self, grow, add; };   // grow = s (d - 1), add = v s
+// LDS stride s amplitudes, is inserted into j by ascending stride.
 struct Op {
   uint32_t dT;             // amplitudes per slice (the in-window targets)
   uint32_t kind;           // kMove: every entry 1, kMono: one entry per column, kDense: dT x dT
@@ -461,8 +459,7 @@ static bool build_op(const Register& r, const Gate& p, uint64_t window, const st
   for (int q : order) {   // by ascending LDS stride
     if (!fixed[q] && !target[q]) continue;
     const uint32_t st = lst[q];
-    (op->nins < 2 ? op->ins[op->nins] : rest->more[op->nins - 2]) = {st > 1 ? uint32_t((uint64_t(1) << 32) / st) + 1u : 0u, st > 1 ? 0u : ~0u,
-                           st * uint32_t(r.dims[q] - 1), value[q] * st};
+    (op->nins < 2 ? op->ins[op->nins] : rest->more[op->nins - 2]) = make_insert(st, uint32_t(r.dims[q]), value[q]);
     ++op->nins;
   }
   return true;

@@ -433,6 +433,37 @@ def test_gemm_route_sizes(stream, prec):
 
 @pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
 @pytest.mark.parametrize("dims, t, c, v", [
+    ((3, 2, 2, 5, 2, 3, 2, 2, 2), (8, 5), (7, 6, 4), (1, 0, 1)),      # five digits inserted, controls below one line
+    ((3, 2, 2, 5, 2, 3, 2, 2, 2), (8, 0), (7,), (1,)),                # a high target: several runs a tile
+    ((7, 2, 3, 2, 3, 2, 2, 2, 3, 2), (9, 1), (4, 6, 8), (2, 1, 0)),   # left-out and staged controls together
+    ((3,) * 7 + (2,), (7,), (), ()),                                  # stride 1
+    ((5, 7, 5, 7, 5, 2), (5, 4), (), ()),                             # 10 x 10: matrix cores
+    ((5, 7, 5, 7, 9), (4,), (), ()),                                  # one qudit of 9 at stride 1
+    ((2,) * 13, (12, 11, 10), (0,), (0,)),
+])
+@pytest.mark.parametrize("kind", ["dense", "shift"])
+def test_tiled_inserted_digits(stream, prec, dims, t, c, v, kind):
+    """The LDS tile kernel's slice index (target and control digits inserted into the slice number) with
+    up to five digits, one run or several a tile, dense and monomial, against the oracle."""
+    rng = C.seeded_rng(94)
+    D = O.register_size(dims)
+    psi0 = rng.standard_normal(D) + 1j * rng.standard_normal(D)
+    psi0 /= np.linalg.norm(psi0)
+    dT = int(np.prod([dims[q] for q in t]))
+    U = C.haar_unitary(dT, rng) if kind == "dense" else np.eye(dT)[rng.permutation(dT)] * np.exp(1j * rng.random(dT))
+    s = Q.qd_state_init(dims, prec, stream)
+    try:
+        Q.qd_state_upload(s, psi0)
+        Q.qd_apply_gate(s, t, c, v, U)
+        out = Q.qd_state_download(s)
+    finally:
+        Q.qd_state_free(s)
+    ref = O.apply_gate(psi0, dims, t, c, v, U)
+    assert max_abs(out, ref) <= (1e-12 if prec == Q.QD_C128 else c64_tol(1, dT)), (t, c, dT, prec)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("dims, t, c, v", [
     ((2, 11, 2, 5, 3, 7, 2, 3, 2, 5, 3), (1,), (), ()),            # d_T = 11: 128 slices a tile, ragged
     ((2, 11, 2, 5, 3, 7, 2, 3, 2, 5, 3), (9, 10), (0,), (1,)),     # d_T = 15, lowest targets, a control
     ((17, 2, 3, 5, 2, 3, 7, 2, 3, 2), (0,), (), ()),               # one past a 16-row tile, 32 slices a tile
