@@ -248,6 +248,7 @@ struct Gate {           // a gate as the planner sees it
   int cls = 0, dT = 0;
   double act = 1.0;          // share of the amplitudes whose control digits match
   bool fits = false;         // some window can hold it
+  bool exact = false;        // it only moves amplitudes: no rounding
 };
 
 struct Pass {
@@ -295,10 +296,13 @@ static double cost_inside(const Gate& p, double bytes, double D) {
 static double cost_window(double bytes) { return 5.5 + bytes / 5e6; }
 
 // Cuts the list into passes whose windows hold at most emax amplitudes: a pass takes the first gate not
-// yet placed and every later one that fits its window and commutes with the gates it moves ahead of.
+// yet placed and every later one that fits its window and commutes with the gates it moves ahead of;
+// with `in_order` (complex64) no gate that rounds moves ahead of another, so that a circuit leaves the bits
+// that its gates leave one by one: what a program reads back in 64 bits would show the difference. Moves
+// alone still change places. (3^13, 100 named gates: 932 us one by one, 290 so.)
 // *cost receives the estimate of all passes.
 static std::vector<Pass> plan_passes(const Register& r, const std::vector<Gate>& gate, int pq0, uint64_t emax, double bytes,
-                                     double* cost) {
+                                     bool in_order, double* cost) {
   const size_t n = gate.size();
   const uint64_t suf0 = suffix_mask(r, pq0), all = r.n == 64 ? ~uint64_t(0) : (uint64_t(1) << r.n) - 1;
   std::vector<Pass> passes;
@@ -308,6 +312,7 @@ static std::vector<Pass> plan_passes(const Register& r, const std::vector<Gate>&
     Pass ps;
     ps.pq = pq0;
     uint64_t w = suf0 | gate[first].nd, E = span_of(r, w), skip_nd = 0, skip_any = 0;
+    bool rounds = false;   // a gate left behind rounds
     ps.gates.push_back(int(first));
     placed[first] = 1;
     if (gate[first].fits && E <= emax)
@@ -315,7 +320,7 @@ static std::vector<Pass> plan_passes(const Register& r, const std::vector<Gate>&
         if (placed[i]) continue;
         ++looked;
         const Gate& it = gate[i];
-        if (it.fits && !((it.nd | it.dg) & skip_nd) && !(it.nd & skip_any)) {
+        if (it.fits && !((it.nd | it.dg) & skip_nd) && !(it.nd & skip_any) && !(in_order && rounds && !it.exact)) {
           const uint64_t grow = (it.nd & ~w) ? span_of(r, it.nd & ~w) : 1;
           if (E * grow <= emax) {
             w |= it.nd;
@@ -327,6 +332,7 @@ static std::vector<Pass> plan_passes(const Register& r, const std::vector<Gate>&
         }
         skip_nd |= it.nd;
         skip_any |= it.nd | it.dg;
+        rounds = rounds || !it.exact;
         if ((skip_nd & all) == all) break;
       }
     double one = 0.0, together = cost_window(bytes);
@@ -516,6 +522,17 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
     p.dT = 1;
     for (int j = 0; j < p.g->k; ++j) p.dT *= r.dims[p.g->t[j]];
     p.cls = classify(p.g->U, p.dT);
+    if (p.cls == QD_CLASS_MONOMIAL) {
+      p.exact = true;
+      for (int e = 0; e < p.dT * p.dT; ++e)
+        p.exact = p.exact && p.g->U[2 * e + 1] == 0.0 && (p.g->U[2 * e] == 0.0 || p.g->U[2 * e] == 1.0);
+      // one that rounds is mixed as a dense gate wherever the gate by itself would be
+      if (!dbl && !p.exact) {
+        GatePlan alone_plan;
+        plan_gate(r, s->prec, p.g->t, p.g->k, p.g->c, p.g->v, p.g->m, p.g->U, &alone_plan);
+        if (route_gate(r, s->prec, alone_plan) == QD_ROUTE_DIRECT && alone_plan.dT <= 9) p.cls = QD_CLASS_DENSE;
+      }
+    }
     for (int j = 0; j < p.g->k; ++j) (p.cls == QD_CLASS_DIAGONAL ? p.dg : p.nd) |= uint64_t(1) << p.g->t[j];
     for (int j = 0; j < p.g->m; ++j) {
       p.dg |= uint64_t(1) << p.g->c[j];
@@ -534,10 +551,10 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
   const uint64_t most = dbl ? kTile : 2 * kTile, D = uint64_t(r.D);
   const uint64_t emax = D <= most ? most : std::min(most, std::max<uint64_t>(1024, D / 256));
   double cost = 0.0;
-  std::vector<Pass> passes = plan_passes(r, gate, pq0, emax, bytes, &cost);
+  std::vector<Pass> passes = plan_passes(r, gate, pq0, emax, bytes, !dbl, &cost);
   if (D >= 512 * most) {
     double half = 0.0;
-    std::vector<Pass> other = plan_passes(r, gate, pq0, most / 2, bytes, &half);
+    std::vector<Pass> other = plan_passes(r, gate, pq0, most / 2, bytes, !dbl, &half);
     if (0.94 * half < cost) passes.swap(other);
   }
 

@@ -163,3 +163,31 @@ def test_circuit_captured_in_a_graph():
         Q.qd_state_free(t)
         Q.qd_circuit_free(c)
         Q.qd_circuit_free(other)
+
+
+@pytest.mark.parametrize("dims, n, controls", [
+    ((3,) * 8, 60, 2),
+    ((2, 3, 2, 4, 3, 2, 3, 2, 3, 4, 2, 3), 80, 2),
+    ((5, 7, 2, 3, 4, 2, 3, 2, 2), 60, 3),
+    ((12, 9, 16, 2, 3), 40, 1),
+])
+def test_complex64_circuit_leaves_the_bits_of_its_gates(stream, dims, n, controls):
+    """A complex64 circuit applied in windows moves no rounding gate ahead of another, and each gate makes
+    the same sums in a window as by itself: not one bit may differ from the gates one call at a time."""
+    rng = np.random.default_rng(sum(dims) + 7)
+    c, gates = named_circuit(dims, n, rng, controls)
+    D = O.register_size(dims)
+    psi0 = (rng.normal(size=D) + 1j * rng.normal(size=D)) / np.sqrt(2.0 * D)
+    psi0 = psi0.astype(np.complex64)
+    s, one = Q.qd_state_init(dims, Q.QD_C64, stream), Q.qd_state_init(dims, Q.QD_C64, stream)
+    try:
+        for h in (s, one):
+            Q.qd_state_upload(h, psi0)
+        Q.qd_circuit_apply(s, c)
+        for g in gates:
+            Q.apply_circuit_gate(one, g, dims)
+        assert np.array_equal(Q.qd_state_download(s), Q.qd_state_download(one))
+    finally:
+        Q.qd_state_free(s)
+        Q.qd_state_free(one)
+        Q.qd_circuit_free(c)
