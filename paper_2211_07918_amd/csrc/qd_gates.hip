@@ -95,6 +95,13 @@ __device__ __forceinline__ void put(C* p, int64_t i, C v) {
   else p[i] = v;
 }
 
+// get: an amplitude from HBM (ST: streaming load)
+template <bool ST, typename C>
+__device__ __forceinline__ C get(const C* p) {
+  if constexpr (ST) return ld_stream(p);
+  else return *p;
+}
+
 template <bool ST, typename C, typename R, int DT>
 __device__ __forceinline__ void mix_store(C* p, int64_t base, const int64_t* toff, const int64_t*,
                                           const DenseOp<R, DT>& op, const C (&x)[DT]) {
@@ -213,7 +220,7 @@ __device__ __forceinline__ void mix_select(const MonoOp<R, DT>& op, const C (&x)
   }
 }
 
-template <typename R, int DT, typename OP, int SPT, int MODE>
+template <typename R, int DT, typename OP, int SPT, int MODE, bool ST>
 __global__ __launch_bounds__(256) void k_slices_direct(DirectArgs<R, DT, OP> a) {
   using C = typename CxT<R>::T;
   C* __restrict__ psi = reinterpret_cast<C*>(a.psi);
@@ -270,12 +277,12 @@ __global__ __launch_bounds__(256) void k_slices_direct(DirectArgs<R, DT, OP> a) 
     for (int y = 0; y < DT; ++y) {
       x[y].x = R(0);
       x[y].y = R(0);
-      if (valid & (1u << y)) x[y] = ld_stream(psi + pos + a.toff[y]);
+      if (valid & (1u << y)) x[y] = get<ST>(psi + pos + a.toff[y]);
     }
     mix_select<C, R, DT>(a.op, x, act, out);
 #pragma unroll
     for (int y = 0; y < DT; ++y)
-      if (valid & (1u << y)) st_stream(psi + pos + a.toff[y], out[y]);
+      if (valid & (1u << y)) put<ST>(psi, pos + a.toff[y], out[y]);
   } else {
     const uint64_t first = uint64_t(blockIdx.x) * bs * SPT + threadIdx.x;
     int64_t base[SPT];
@@ -289,11 +296,11 @@ __global__ __launch_bounds__(256) void k_slices_direct(DirectArgs<R, DT, OP> a) 
     for (int s = 0; s < SPT; ++s)
       if (base[s] >= 0) {
 #pragma unroll
-        for (int y = 0; y < DT; ++y) x[s][y] = ld_stream(psi + base[s] + a.toff[y]);
+        for (int y = 0; y < DT; ++y) x[s][y] = get<ST>(psi + base[s] + a.toff[y]);
       }
 #pragma unroll
     for (int s = 0; s < SPT; ++s)
-      if (base[s] >= 0) mix_store<true, C, R, DT>(psi, base[s], a.toff, a.doff, a.op, x[s]);
+      if (base[s] >= 0) mix_store<ST, C, R, DT>(psi, base[s], a.toff, a.doff, a.op, x[s]);
   }
 }
 
@@ -306,7 +313,7 @@ struct LuHead {
   // followed by 2 DT^2 values of R (U, row-major interleaved)
 };
 
-template <typename R, int DT>
+template <typename R, int DT, bool ST>
 __global__ __launch_bounds__(256) void k_slices_direct_lu(R* psi_raw, const unsigned char* desc) {
   using C = typename CxT<R>::T;
   __shared__ R su[2 * DT * DT];
@@ -327,7 +334,7 @@ __global__ __launch_bounds__(256) void k_slices_direct_lu(R* psi_raw, const unsi
   const int64_t b = sm_offset(smap, uint32_t(i));
   C x[DT];
 #pragma unroll
-  for (int y = 0; y < DT; ++y) x[y] = ld_stream(psi + b + st[y]);
+  for (int y = 0; y < DT; ++y) x[y] = get<ST>(psi + b + st[y]);
 #pragma unroll
   for (int r = 0; r < DT; ++r) {
     __asm__ volatile("" ::: "memory");   // U is read from LDS here (held in registers it would take hundreds)
@@ -343,7 +350,7 @@ __global__ __launch_bounds__(256) void k_slices_direct_lu(R* psi_raw, const unsi
     C yv;
     yv.x = re;
     yv.y = im;
-    st_stream(psi + b + st[r], yv);
+    put<ST>(psi, b + st[r], yv);
   }
 }
 
@@ -394,7 +401,7 @@ template <> struct TileEpt<float> { static constexpr int value = 16; };
 template <typename OP> struct DenseDim { static constexpr int value = 0; };
 template <typename R, int DT> struct DenseDim<DenseOp<R, DT>> { static constexpr int value = DT; };
 
-template <typename R, int DT, typename OP>
+template <typename R, int DT, typename OP, bool ST>
 __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
   using C = typename CxT<R>::T;
   constexpr int EPT = TileEpt<R>::value;
@@ -455,7 +462,7 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
 #pragma unroll
       for (int e = 0; e < EPT; ++e)
         if (uint32_t(e) * bs < E) {
-          const C t = ld_stream(byte_at(min(tl + e * bs, E - 1)));
+          const C t = get<ST>(byte_at(min(tl + e * bs, E - 1)));
           vr[e] = t.x;
           vi[e] = t.y;
         }
@@ -463,7 +470,7 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
 #pragma unroll
       for (int e = 0; e < EPT; ++e)
         if (tl + e * bs < E) {
-          const C t = ld_stream(p0 + place(tl + e * bs));
+          const C t = get<ST>(p0 + place(tl + e * bs));
           vr[e] = t.x;
           vi[e] = t.y;
         }
@@ -538,7 +545,7 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
       C t;
       t.x = vr[e];
       t.y = vi[e];
-      st_stream(p, t);
+      put<ST>(p, 0, t);
     };
     if (whole) {
 #pragma unroll
@@ -561,7 +568,7 @@ struct DiagArgs {
   R ph[2 * kMaxInlineTable];       // phase of target combination loc
 };
 
-template <typename R, int SPT>
+template <typename R, int SPT, bool ST>
 __global__ __launch_bounds__(256) void k_diag(DiagArgs<R> a) {
   using C = typename CxT<R>::T;
   C* __restrict__ psi = reinterpret_cast<C*>(a.psi);
@@ -577,7 +584,7 @@ __global__ __launch_bounds__(256) void k_diag(DiagArgs<R> a) {
   }
 #pragma unroll
   for (int s = 0; s < SPT; ++s)
-    if (off[s] >= 0) x[s] = ld_stream(psi + off[s]);
+    if (off[s] >= 0) x[s] = get<ST>(psi + off[s]);
 #pragma unroll
   for (int s = 0; s < SPT; ++s)
     if (off[s] >= 0) {
@@ -585,7 +592,7 @@ __global__ __launch_bounds__(256) void k_diag(DiagArgs<R> a) {
       C y;
       y.x = fma(pr, x[s].x, -pi * x[s].y);
       y.y = fma(pr, x[s].y, pi * x[s].x);
-      st_stream(psi + off[s], y);
+      put<ST>(psi, off[s], y);
     }
 }
 
@@ -651,28 +658,42 @@ __global__ __launch_bounds__(256) void k_dense_generic(R* psi_raw, const unsigne
 //   - X (all d_T amplitudes of ns slices) is staged in LDS once, pitch ns + 1 so that both loading
 //     orders and the operand reads spread over the banks; every output of those slices is made by
 //     this workgroup, so the results go from the accumulators straight back to HBM.
-//   - U is stored by the host in operand order (lane l of K step k holds row l & 15, column
-//     4 k + (l >> 4)), one coalesced 16-byte (8-byte) load per lane and step, four steps ahead. It is
-//     read from L2 by every workgroup: at 16 slices or more per tile that is at most 1 KB per 256
-//     matrix-core cycles of a SIMD. So U takes no LDS and d_T is bounded by X alone.
+//   - The matrix cores sum the four products of a K step as a chain of fused multiply-adds in ascending K
+//     (checked bit for bit against such chains in both precisions). complex64 takes two columns a step,
+//     real and imaginary part by turns: every output is then the very sum that a thread of the
+//     vector-unit kernels makes, column by column in listed order, and no bit of a complex64 state
+//     depends on the kernel that a gate takes. Its operands cost twice the LDS reads, which is why
+//     complex128, where the order moves a result by 1e-16, takes four columns a step: all their real
+//     parts, then all their imaginary ones (4^12, d_T = 64 and 256: complex64 124 -> 141, 552 -> 702 us,
+//     complex128 would go 187 -> 201, 842 -> 996).
+//   - U is stored by the host in operand order (lane l of a K step holds row l & 15 and, in complex128,
+//     column 4 k + (l >> 4), in complex64 one part of column 2 k + (l >> 5)), one coalesced load per
+//     lane and step, four steps ahead. It is read from L2 by every workgroup: at 16 slices or more per
+//     tile that is at most 1 KB per 256 matrix-core cycles of a SIMD. So U takes no LDS and d_T is
+//     bounded by X alone.
 //   - A job is one 16-row tile of U times CG column tiles; the waves of a workgroup share them.
-// The operands of a product may change places, which transposes the result: with kYF the 16
+// The operands of a product may change places, which transposes the result: with kMfmaYF the 16
 // consecutive lanes of a store hold consecutive target combinations (a target has the smallest
 // stride) instead of consecutive slices, so both kinds of gate store runs.
 // Measured, complex128 (kernel time; before: a vector-unit GEMM with U and X in LDS up to d_T = 64,
 // above it a kernel that read U from L2 for every product): on 3^14 amplitudes d_T = 27 76 -> 49 us,
 // 81 880 -> 92 us, 243 5220 -> 195 us (48 TFLOP/s); on 4^12 amplitudes d_T = 64 360 -> 189 us, 256
 // 16.4 -> 0.60 ms (57 TFLOP/s); on the hybrid register of 1.1e8 amplitudes d_T = 27 1083 -> 757 us
-// (4.5 TB/s), 54 2160 -> 1119 us. complex64 on 4^12: 64 205 -> 110 us, 256 15.2 -> 0.34 ms.
+// (4.5 TB/s), 54 2160 -> 1119 us. complex64 on 4^12: 64 205 -> 141 us, 256 15.2 -> 0.70 ms.
+// Lines that belong to several runs (a target or control stride that is no multiple of a line) are read
+// and written with plain accesses, so that the cache merges their parts: streaming stores cost up to a
+// line each (d_T = 27 on 3^16, lowest targets of stride 3, 27 and 3^13: complex64 464, 384, 249 -> 236,
+// 233, 225 us, complex128 480, 450, 410 -> 367, 348, 341). Whole lines stream: 395 against 413 us for
+// d_T = 64 with stride 16 on 4^13 in complex64, 774 against 823 for d_T = 27 on the hybrid register.
 constexpr int kGemmMin = 10;
 constexpr int kGemmMax = 64;
 
 struct MfmaArgs {
   SliceMap sm;                        // slices: the non-target digits (controls fixed)
   Magic32 div;                        // division by ns, or by KP when target combinations are fastest
-  uint32_t dT, KP, RT, ns, njobs;     // KP: d_T rounded up to 4; RT: 16-row tiles of U; jobs per tile
-  const unsigned char* desc;          // int64_t toff[d_T] by ascending offset, then (16-byte aligned)
-                                      // RT x KP/4 x 64 entries of U in operand order, in that order
+  uint32_t dT, KP, RT, ns, njobs;     // KP: d_T rounded up to whole K steps; RT: 16-row tiles of U; jobs per tile
+  const unsigned char* desc;          // uint64_t[d_T], by ascending offset: the offset and (upper half) the
+                                      // column; then (16-byte aligned) RT x K steps x 64 entries of U in operand order
 };
 
 template <typename R> struct Mfma16;
@@ -687,19 +708,25 @@ template <> struct Mfma16<float> {
   static __device__ __forceinline__ uint32_t row(uint32_t i, uint32_t q) { return 4u * q + i; }
 };
 
-template <typename R, int CG, bool YF>
+enum { kMfmaYF, kMfmaLines, kMfmaParts };
+template <typename R> constexpr uint32_t kMfmaStep = sizeof(R) == 8 ? 4 : 2;   // columns of U a K step
+
+template <typename R, int CG, int MODE>
 __global__ __launch_bounds__(1024) void k_dense_mfma(R* psi_raw, MfmaArgs a) {
   using C = typename CxT<R>::T;
   using M = Mfma16<R>;
   using V4 = typename M::V4;
+  constexpr bool YF = MODE == kMfmaYF;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   C* __restrict__ psi = reinterpret_cast<C*>(psi_raw);
   const uint32_t dT = a.dT, KP = a.KP, ns = a.ns, P = ns + 1, bs = blockDim.x, tid = threadIdx.x;
   C* xs = reinterpret_cast<C*>(lds_raw);                        // KP x ns, element (y, j) at y P + j
   int64_t* sb = reinterpret_cast<int64_t*>(xs + KP * P + (KP * P & 1u));   // ns slice bases
-  int64_t* to = sb + ns;                                        // d_T target offsets
-  const int64_t* tg = reinterpret_cast<const int64_t*>(a.desc);
-  const C* ug = reinterpret_cast<const C*>(a.desc + ((sizeof(int64_t) * dT + 15) & ~size_t(15)));
+  uint64_t* to = reinterpret_cast<uint64_t*>(sb + ns);          // d_T target offsets (low half) and columns
+  const uint64_t* tg = reinterpret_cast<const uint64_t*>(a.desc);
+  // an entry of U in operand order: both parts of one column, or one part (kMfmaStep columns a step)
+  using U = typename std::conditional<kMfmaStep<R> == 4, C, R>::type;
+  const U* ug = reinterpret_cast<const U*>(a.desc + ((sizeof(int64_t) * dT + 15) & ~size_t(15)));
   const uint32_t s0 = blockIdx.x * ns, nsv = min(ns, a.sm.count - s0);   // nsv: slices of this tile
   // a column past the last slice repeats it (read, multiplied and not stored): no load is conditional
   for (uint32_t j = tid; j < ns; j += bs) sb[j] = sm_offset(a.sm, s0 + min(j, nsv - 1));
@@ -718,11 +745,12 @@ __global__ __launch_bounds__(1024) void k_dense_mfma(R* psi_raw, MfmaArgs a) {
       const uint32_t q = magic_div(e, a.div), r = e - q * a.div.d;
       const uint32_t y = YF ? r : q, j = YF ? q : r;
       pad[k] = y >= dT;
-      at[k] = y * P + j;
-      off[k] = sb[j] + to[pad[k] ? dT - 1 : y];
+      const uint64_t t = to[pad[k] ? dT - 1 : y];
+      at[k] = (pad[k] ? y : uint32_t(t >> 32)) * P + j;
+      off[k] = sb[j] + uint32_t(t);
     }
 #pragma unroll
-    for (int k = 0; k < B; ++k) v[k] = ld_stream(psi + off[k]);
+    for (int k = 0; k < B; ++k) v[k] = MODE == kMfmaParts ? psi[off[k]] : ld_stream(psi + off[k]);
 #pragma unroll
     for (int k = 0; k < B; ++k) {
       if (pad[k]) v[k].x = v[k].y = R(0);
@@ -731,48 +759,60 @@ __global__ __launch_bounds__(1024) void k_dense_mfma(R* psi_raw, MfmaArgs a) {
   }
   __syncthreads();
   const uint32_t lane = tid & 63u, lq = lane >> 4, lr = lane & 15u, nw = bs >> 6;
-  const uint32_t KS = KP / 4;
+  const uint32_t KS = KP / kMfmaStep<R>;
   for (uint32_t job = tid >> 6; job < a.njobs; job += nw) {   // wave-uniform
     const uint32_t cj = job / a.RT, rt = job - cj * a.RT;
-    const C* up = ug + size_t(rt) * KS * 64 + lane;
-    const C* xp = xs + lq * P + cj * (16u * CG) + lr;
+    const U* up = ug + size_t(rt) * KS * 64 + lane;
+    const C* xp = xs + (kMfmaStep<R> == 4 ? lq : lq >> 1) * P + cj * (16u * CG) + lr;
     V4 re[CG], im[CG];
 #pragma unroll
     for (int g = 0; g < CG; ++g) {
       re[g] = V4{R(0), R(0), R(0), R(0)};
       im[g] = re[g];
     }
-    auto ldu = [&](C (&u)[4], uint32_t k0) {   // four steps of U (past the last one: that one again)
+    constexpr uint32_t N = 4;
+    auto ldu = [&](U (&u)[N], uint32_t k0) {   // N steps of U (past the last one: that one again)
 #pragma unroll
-      for (uint32_t k = 0; k < 4; ++k) u[k] = up[64 * min(k0 + k, KS - 1)];
+      for (uint32_t k = 0; k < N; ++k) u[k] = up[64 * min(k0 + k, KS - 1)];
     };
-    auto step = [&](C u, uint32_t ks) {
+    auto mul = [&](R u, R x, V4 c) { return YF ? M::mul(x, u, c) : M::mul(u, x, c); };
+    auto step = [&](U u, uint32_t ks) {
       C x[CG];
 #pragma unroll
-      for (int g = 0; g < CG; ++g) x[g] = xp[ks * 4 * P + 16 * g];
+      for (int g = 0; g < CG; ++g) x[g] = xp[ks * kMfmaStep<R> * P + 16 * g];
+      if constexpr (kMfmaStep<R> == 4) {
 #pragma unroll
-      for (int g = 0; g < CG; ++g) {
-        re[g] = YF ? M::mul(x[g].x, u.x, re[g]) : M::mul(u.x, x[g].x, re[g]);
-        im[g] = YF ? M::mul(x[g].y, u.x, im[g]) : M::mul(u.x, x[g].y, im[g]);
-      }
+        for (int g = 0; g < CG; ++g) {
+          re[g] = mul(u.x, x[g].x, re[g]);
+          im[g] = mul(u.x, x[g].y, im[g]);
+        }
 #pragma unroll
-      for (int g = 0; g < CG; ++g) {
-        re[g] = YF ? M::mul(x[g].y, -u.y, re[g]) : M::mul(-u.y, x[g].y, re[g]);
-        im[g] = YF ? M::mul(x[g].x, u.y, im[g]) : M::mul(u.y, x[g].x, im[g]);
+        for (int g = 0; g < CG; ++g) {
+          re[g] = mul(-u.y, x[g].y, re[g]);
+          im[g] = mul(u.y, x[g].x, im[g]);
+        }
+      } else {
+        const bool odd = (lq & 1u) != 0;   // this lane holds an imaginary part of U
+        const R v = odd ? -u : u;
+#pragma unroll
+        for (int g = 0; g < CG; ++g) {
+          re[g] = mul(v, odd ? x[g].y : x[g].x, re[g]);
+          im[g] = mul(u, odd ? x[g].x : x[g].y, im[g]);
+        }
       }
     };
-    auto four = [&](const C (&u)[4], uint32_t k0) {
+    auto many = [&](const U (&u)[N], uint32_t k0) {
 #pragma unroll
-      for (uint32_t k = 0; k < 4; ++k)
+      for (uint32_t k = 0; k < N; ++k)
         if (k0 + k < KS) step(u[k], k0 + k);
     };
-    C ua[4], ub[4];
+    U ua[N], ub[N];
     ldu(ua, 0);
-    for (uint32_t ks = 0; ks < KS; ks += 8) {
-      ldu(ub, ks + 4);
-      four(ua, ks);
-      ldu(ua, ks + 8);
-      four(ub, ks + 4);
+    for (uint32_t ks = 0; ks < KS; ks += 2 * N) {
+      ldu(ub, ks + N);
+      many(ua, ks);
+      ldu(ua, ks + 2 * N);
+      many(ub, ks + N);
     }
     // lane lr of a store holds consecutive slices (or consecutive target combinations): the four rows
     // of a register tile are four stores
@@ -782,7 +822,7 @@ __global__ __launch_bounds__(1024) void k_dense_mfma(R* psi_raw, MfmaArgs a) {
     for (uint32_t i = 0; i < 4; ++i) {
       const uint32_t y = rt * 16u + (YF ? lr : M::row(i, lq));
       rv[i] = y < dT;
-      ro[i] = to[min(y, dT - 1)];
+      ro[i] = uint32_t(to[min(y, dT - 1)]);
     }
 #pragma unroll
     for (int g = 0; g < CG; ++g) {
@@ -795,9 +835,9 @@ __global__ __launch_bounds__(1024) void k_dense_mfma(R* psi_raw, MfmaArgs a) {
         v.x = re[g][i];
         v.y = im[g][i];
         if (rv[i] && j < nsv) {
-          // runs of target combinations end inside lines, which the cache merges across row tiles
-          if constexpr (YF) psi[o] = v;
-          else st_stream(psi + o, v);
+          // runs of target combinations end inside lines too
+          if constexpr (MODE == kMfmaLines) st_stream(psi + o, v);
+          else psi[o] = v;
         }
       }
     }
@@ -1009,6 +1049,33 @@ static void fill_doff(const GatePlan& p, const int64_t* toff, int64_t* doff) {
   for (int c = 0; c < DT; ++c) doff[c] = p.dst.empty() ? 0 : toff[p.dst[c]];
 }
 
+// Whether a pass goes by the caches (streaming loads and stores) or leaves its lines in them.
+//   - Touched amplitudes of at most 256 MB (the size of the card's last-level cache) stay there for the
+//     next pass: plain accesses win 4 to 20 % (complex128: a qubit of 2^24 94 -> 86 us, pairs 106 -> 88,
+//     qutrits of 3^15 90 to 102 -> 77 to 79; complex64: 2^25 97 -> 89, 3^15 50 to 59 -> 44) and lose as
+//     much right above it (2^25 complex128 175 -> 190, 2^26 complex64 180 -> 196). Passes of 32 MB or
+//     less stay streaming: what the L2s (8 x 4 MB) hold is written back at the end of each kernel
+//     anyway, and 2^20 in complex128 lost 1 to 2 of 14 us.
+//   - Above it, one slice a thread whose planes begin inside 64-byte sectors: the ends of a wave's runs
+//     share sectors with the next wave's, and a streaming store of part of one costs a whole one.
+//     complex64, where a wave writes 512 bytes, always wins by plain accesses (9 x 9 gates on 3^17 475
+//     and 533 -> 404 and 395 us, a unit of 7^9 148 -> 120); complex128 up to strides of 512 (9 x 9 on
+//     3^16 294 -> 273, a qutrit of stride 27 289 -> 260) and not above (250 -> 272, 745 -> 827 on 3^17).
+static bool streaming(const qd_state* s, const GatePlan& p, uint64_t touched, bool direct) {
+  const uint64_t amp = uint64_t(amp_bytes(s->prec));
+  if (touched * amp <= uint64_t(32) << 20) return true;
+  if (touched * amp <= uint64_t(256) << 20) return false;
+  if (!direct) return true;
+  bool sectors = true;
+  int64_t lowest = INT64_MAX;
+  for (int j = 0; j < p.k + p.m; ++j) {
+    const int64_t st = s->reg.strides[j < p.k ? p.targets[j] : p.controls[j - p.k]];
+    sectors = sectors && uint64_t(st) * amp % 64 == 0;
+    lowest = std::min(lowest, st);
+  }
+  return sectors || (s->prec == QD_C128 && lowest > 512);
+}
+
 template <typename R, int DT, typename OP>
 static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
   const Register& r = s->reg;
@@ -1106,7 +1173,10 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
       const size_t lds = size_t(BL * dH) * sizeof(R) * 2;
       // workgroups walk the tiles; at most 2^22 of them keep the grid inside 32-bit work-item counts
       const unsigned grid = unsigned(std::min<uint64_t>(a.tiles.count, uint64_t(1) << 22));
-      hipLaunchKernelGGL((k_slices_tiled<R, DT, OP>), dim3(grid), dim3(ent.block), lds, s->stream, a);
+      if (streaming(s, p, a.tiles.count * BL * dH, false))
+        hipLaunchKernelGGL((k_slices_tiled<R, DT, OP, true>), dim3(grid), dim3(ent.block), lds, s->stream, a);
+      else
+        hipLaunchKernelGGL((k_slices_tiled<R, DT, OP, false>), dim3(grid), dim3(ent.block), lds, s->stream, a);
       g_last_kernel = label<kKnTiled, R, DT, OP>();
       return check_launch("k_slices_tiled");
     }
@@ -1161,11 +1231,15 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
       spt = min_stride >= 4096 && DT < 4 ? 1 : 2;
     }
   }
+  const bool st = streaming(s, p, uint64_t(a.sm.count) * DT, nlow == 0);
+  auto launch = [&](auto k, uint64_t items, uint64_t per_thread) {
+    hipLaunchKernelGGL(k, dim3(grid_for(items, uint64_t(bs) * per_thread)), dim3(bs), 0, s->stream, a);
+  };
   if (nlow) {
     line_pattern(r, p, line, &a.lper, &a.lmask);
     if (a.lper > 1) a.lpm = make_magic32(a.lper);
-    hipLaunchKernelGGL((k_slices_direct<R, DT, OP, 1, kDirectPred>), dim3(grid_for(a.sm.count, uint64_t(bs))), dim3(bs), 0,
-                       s->stream, a);
+    if (st) launch(k_slices_direct<R, DT, OP, 1, kDirectPred, true>, a.sm.count, 1);
+    else launch(k_slices_direct<R, DT, OP, 1, kDirectPred, false>, a.sm.count, 1);
     g_last_kernel = label<kKnDirect, R, DT, OP, 1, kDirectPred>();
     return check_launch("k_slices_direct");
   }
@@ -1185,8 +1259,9 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
       a.blen = uint32_t(sc);
       a.nvirt = uint32_t(nblk * W);
       a.D = r.D;
-      hipLaunchKernelGGL((k_slices_direct<R, DT, OP, 1, kDirectEdge>), dim3(grid_for(a.nvirt, uint64_t(bs))), dim3(bs), 0,
-                         s->stream, a);
+      // (its edge lanes complete the lines, so only the touched size decides)
+      if (streaming(s, p, uint64_t(a.sm.count) * DT, false)) launch(k_slices_direct<R, DT, OP, 1, kDirectEdge, true>, a.nvirt, 1);
+      else launch(k_slices_direct<R, DT, OP, 1, kDirectEdge, false>, a.nvirt, 1);
       g_last_kernel = label<kKnDirect, R, DT, OP, 1, kDirectEdge>();
       return check_launch("k_slices_direct");
     }
@@ -1194,16 +1269,16 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
   // Several slices per thread only up to d_T = 4: beyond, two slices' operands and the gate's
   // kernel arguments overflow the scalar registers and the spilled values are read back per FMA.
   if (spt >= 4 && DT <= 4) {
-    hipLaunchKernelGGL((k_slices_direct<R, DT, OP, 4, kDirectPlain>), dim3(grid_for(a.sm.count, uint64_t(bs) * 4)), dim3(bs),
-                       0, s->stream, a);
+    if (st) launch(k_slices_direct<R, DT, OP, 4, kDirectPlain, true>, a.sm.count, 4);
+    else launch(k_slices_direct<R, DT, OP, 4, kDirectPlain, false>, a.sm.count, 4);
     g_last_kernel = label<kKnDirect, R, DT, OP, 4, kDirectPlain>();
   } else if (spt >= 2 && DT <= 4) {
-    hipLaunchKernelGGL((k_slices_direct<R, DT, OP, 2, kDirectPlain>), dim3(grid_for(a.sm.count, uint64_t(bs) * 2)), dim3(bs),
-                       0, s->stream, a);
+    if (st) launch(k_slices_direct<R, DT, OP, 2, kDirectPlain, true>, a.sm.count, 2);
+    else launch(k_slices_direct<R, DT, OP, 2, kDirectPlain, false>, a.sm.count, 2);
     g_last_kernel = label<kKnDirect, R, DT, OP, 2, kDirectPlain>();
   } else {
-    hipLaunchKernelGGL((k_slices_direct<R, DT, OP, 1, kDirectPlain>), dim3(grid_for(a.sm.count, uint64_t(bs))), dim3(bs), 0,
-                       s->stream, a);
+    if (st) launch(k_slices_direct<R, DT, OP, 1, kDirectPlain, true>, a.sm.count, 1);
+    else launch(k_slices_direct<R, DT, OP, 1, kDirectPlain, false>, a.sm.count, 1);
     g_last_kernel = label<kKnDirect, R, DT, OP, 1, kDirectPlain>();
   }
   return check_launch("k_slices_direct");
@@ -1245,7 +1320,9 @@ static int launch_diag(qd_state* s, const GatePlan& p) {
   for (int i = 0; i < 2 * p.dT; ++i) a.ph[i] = R(p.ph[i]);
   if (a.sm.count == 0) return QD_OK;
   const int bs = tune().diag_block;
-  hipLaunchKernelGGL((k_diag<R, 2>), dim3(grid_for(a.sm.count, uint64_t(bs) * 2)), dim3(bs), 0, s->stream, a);
+  const dim3 grid(grid_for(a.sm.count, uint64_t(bs) * 2));
+  if (streaming(s, p, a.sm.count, false)) hipLaunchKernelGGL((k_diag<R, 2, true>), grid, dim3(bs), 0, s->stream, a);
+  else hipLaunchKernelGGL((k_diag<R, 2, false>), grid, dim3(bs), 0, s->stream, a);
   g_last_kernel = label<kKnDiag, R>();
   return check_launch("k_diag");
 }
@@ -1302,8 +1379,12 @@ static int launch_direct_lu(qd_state* s, const GatePlan& p) {
   void* dev = nullptr;
   int rc = ring_push(s, buf.data(), bytes, &dev);
   if (rc) return rc;
-  hipLaunchKernelGGL((k_slices_direct_lu<R, DT>), dim3(grid_for(h->sm.count, 256)), dim3(256), 0, s->stream,
-                     reinterpret_cast<R*>(s->data), static_cast<const unsigned char*>(dev));
+  auto launch = [&](auto k) {
+    hipLaunchKernelGGL(k, dim3(grid_for(h->sm.count, 256)), dim3(256), 0, s->stream, reinterpret_cast<R*>(s->data),
+                       static_cast<const unsigned char*>(dev));
+  };
+  if (streaming(s, p, uint64_t(h->sm.count) * DT, true)) launch(k_slices_direct_lu<R, DT, true>);
+  else launch(k_slices_direct_lu<R, DT, false>);
   g_last_kernel = label<kKnLu, R, DT>();
   return check_launch("k_slices_direct_lu");
 }
@@ -1363,45 +1444,44 @@ static int launch_gemm(qd_state* s, const GatePlan& p) {
   MfmaArgs a;
   if (int(groups.size()) > kMaxGroups || fill_slicemap(groups, base, &a.sm) != QD_OK) return launch_generic<R>(s, p);
   if (a.sm.count == 0) return QD_OK;
-  const uint32_t dT = uint32_t(p.dT), KP = (dT + 3) / 4 * 4, KS = KP / 4, RT = (dT + 15) / 16;
+  const uint32_t dT = uint32_t(p.dT), KP = (dT + kMfmaStep<R> - 1) / kMfmaStep<R> * kMfmaStep<R>, KS = KP / kMfmaStep<R>, RT = (dT + 15) / 16;
   const MfmaTile t = mfma_tile(dT, KP, sizeof(C), a.sm.count);
   const uint64_t ntiles = (uint64_t(a.sm.count) + t.ns - 1) / t.ns;
   int64_t tmin = INT64_MAX;
   for (int j = 0; j < p.k; ++j) tmin = std::min<int64_t>(tmin, r.strides[p.targets[j]]);
   const bool yf = groups.empty() || tmin < groups[0].stride;   // groups[0]: the lowest free run
+  bool lines = streaming(s, p, uint64_t(a.sm.count) * dT, false);   // and every run of slices begins and ends on a line
+  for (int j = 0; j < p.k + p.m; ++j)
+    lines = lines && r.strides[j < p.k ? p.targets[j] : p.controls[j - p.k]] % LineAmps<R>::value == 0;
   a.dT = dT;
   a.KP = KP;
   a.RT = RT;
   a.ns = t.ns;
   a.njobs = RT * (std::max(1u, t.ns / 16) / uint32_t(t.cg));
   a.div = make_magic32(yf ? KP : t.ns);
-  // the target combinations by ascending offset: rows and columns of U in that order
+  // the target combinations by ascending offset: the rows of U in that order, its columns as listed
   std::vector<int64_t> toff(dT);
   target_offsets(r, p, toff.data());
   std::vector<int32_t> ord(dT);
   std::iota(ord.begin(), ord.end(), 0);
   std::sort(ord.begin(), ord.end(), [&](int32_t x, int32_t y) { return toff[x] < toff[y]; });
   const size_t uoff = (sizeof(int64_t) * dT + 15) & ~size_t(15);
-  const size_t bytes = uoff + sizeof(C) * size_t(RT) * KS * 64;
+  constexpr uint32_t parts = kMfmaStep<R> / 2;   // of an entry, in one lane
+  const size_t bytes = uoff + sizeof(R) * size_t(RT) * KS * 64 * parts;
   char* host = nullptr;
   char* dev = nullptr;
   int rc = ring_reserve(&s->ring, s->stream, bytes, &host, &dev);
   if (rc) return rc;
-  int64_t* tg = reinterpret_cast<int64_t*>(host);
-  for (uint32_t i = 0; i < dT; ++i) tg[i] = toff[ord[i]];
-  C* ug = reinterpret_cast<C*>(host + uoff);
+  uint64_t* tg = reinterpret_cast<uint64_t*>(host);
+  for (uint32_t i = 0; i < dT; ++i) tg[i] = uint64_t(toff[ord[i]]) | uint64_t(ord[i]) << 32;   // offsets are below 2^32
+  R* ug = reinterpret_cast<R*>(host + uoff);
   for (uint32_t rt = 0; rt < RT; ++rt)
     for (uint32_t ks = 0; ks < KS; ++ks)
       for (uint32_t l = 0; l < 64; ++l) {
-        const uint32_t row = rt * 16 + (l & 15u), col = ks * 4 + (l >> 4);
-        C v;
-        v.x = v.y = R(0);
-        if (row < dT && col < dT) {
-          const double* e = p.U.data() + 2 * (size_t(ord[row]) * dT + ord[col]);
-          v.x = R(e[0]);
-          v.y = R(e[1]);
-        }
-        *ug++ = v;
+        const uint32_t row = rt * 16 + (l & 15u), col = ks * kMfmaStep<R> + (parts == 2 ? l >> 4 : l >> 5);
+        const uint32_t part = parts == 2 ? 0 : l >> 4 & 1u;
+        for (uint32_t i = 0; i < parts; ++i)
+          *ug++ = row < dT && col < dT ? R(p.U[2 * (size_t(ord[row]) * dT + col) + part + i]) : R(0);
       }
   rc = ring_commit(&s->ring, s->stream, host, dev, bytes);
   if (rc) return rc;
@@ -1413,8 +1493,9 @@ static int launch_gemm(qd_state* s, const GatePlan& p) {
     return check_launch("k_dense_mfma");
   };
   g_last_kernel = label<kKnGemm, R>();
-  if (t.cg == 2) return yf ? launch(k_dense_mfma<R, 2, true>) : launch(k_dense_mfma<R, 2, false>);
-  return yf ? launch(k_dense_mfma<R, 1, true>) : launch(k_dense_mfma<R, 1, false>);
+  if (t.cg == 2)
+    return yf ? launch(k_dense_mfma<R, 2, kMfmaYF>) : lines ? launch(k_dense_mfma<R, 2, kMfmaLines>) : launch(k_dense_mfma<R, 2, kMfmaParts>);
+  return yf ? launch(k_dense_mfma<R, 1, kMfmaYF>) : lines ? launch(k_dense_mfma<R, 1, kMfmaLines>) : launch(k_dense_mfma<R, 1, kMfmaParts>);
 }
 
 template <typename R>

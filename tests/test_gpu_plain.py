@@ -733,3 +733,87 @@ def test_inline_controls_take_the_direct_route(stream, prec):
         assert Q.QD_ROUTE_TILED in seen and (prec == Q.QD_C64 or Q.QD_ROUTE_DIRECT in seen)
     finally:
         Q.qd_tune_set(Q.QD_TUNE_RUN_MIN, 0)
+
+
+@pytest.mark.parametrize("dims, t, c, v", [
+    ((4, 3, 4, 2, 3, 2), (0, 2), (), ()),                 # d_T = 16
+    ((5, 3, 7, 2), (2, 0), (), ()),                       # 35, an odd last K step, targets not in offset order
+    ((3, 11, 2, 3), (1,), (3,), (2,)),                    # 11, a control below the target
+    ((2, 3, 5, 3, 5), (2, 4), (0,), (1,)),                # 25, a target of stride 1
+    ((3, 4, 4, 4, 2), (1, 2, 3), (), ()),                 # 64
+])
+def test_complex64_dense_sums_in_listed_order(stream, dims, t, c, v):
+    """Every output of a dense complex64 gate is one chain of float32 fused multiply-adds over the columns
+    in listed order, real then imaginary part: equal to the last bit. (The chains are made in 64-bit
+    mantissas, in which a product of two float32 is exact, and rounded after each addition.)"""
+    rng = C.seeded_rng(95)
+    D = O.register_size(dims)
+    psi0 = (rng.standard_normal(D) + 1j * rng.standard_normal(D)).astype(np.complex64)
+    dT = int(np.prod([dims[q] for q in t]))
+    U = C.haar_unitary(dT, rng)
+    s = Q.qd_state_init(dims, Q.QD_C64, stream)
+    try:
+        Q.qd_state_upload(s, psi0)
+        Q.qd_apply_gate_ex(s, t, c, v, U, Q.QD_FLAG_SKIP_UNITARY_CHECK)
+        out = Q.qd_state_download(s)
+    finally:
+        Q.qd_state_free(s)
+    L, f = np.longdouble, np.float32
+    at = np.arange(D).reshape(dims)
+    for q, val in zip(c, v):
+        at = np.take(at, [val], axis=q)
+    rest = [q for q in range(len(dims)) if q not in t]
+    at = at.transpose(list(t) + rest).reshape(dT, -1)      # listed order of the target combinations
+    x, u = psi0[at], U.astype(np.complex64)
+    ref = psi0.copy()
+    for r in range(dT):
+        re, im = np.zeros(at.shape[1], f), np.zeros(at.shape[1], f)
+        for k in range(dT):
+            ur, ui, xr, xi = L(u[r, k].real), L(u[r, k].imag), x[k].real.astype(L), x[k].imag.astype(L)
+            re = (ur * xr + re).astype(f)
+            re = (-ui * xi + re).astype(f)
+            im = (ur * xi + im).astype(f)
+            im = (ui * xr + im).astype(f)
+        ref[at[r]] = re + 1j * im
+    assert np.array_equal(out, ref)
+
+
+@pytest.mark.parametrize("prec, dims, gates", [
+    # 32 to 256 MB touched: kept in the caches
+    (Q.QD_C128, (2,) * 22, [((3,), ()), ((21,), ()), ((0, 7), (9,)), ((4,), (21,)), ((1, 2, 5, 8), ()), ((0, 1, 2, 3, 20), ())]),
+    (Q.QD_C128, (3,) * 14, [((2,), ()), ((0, 8), ()), ((13,), ()), ((12, 13), (3,)), ((2,), (9,)), ((5, 6, 7), ()), ((1,), (13,))]),
+    (Q.QD_C64, (3,) * 15, [((2,), ()), ((0, 8), ()), ((14,), ()), ((5, 6, 7), ()), ((10, 11, 12), ())]),
+    # above 256 MB: runs inside lines
+    (Q.QD_C64, (3,) * 16, [((11,), ()), ((4, 10), ()), ((15,), ()), ((12, 13, 14), ())]),
+    (Q.QD_C128, (3,) * 15 + (2,), [((11,), ()), ((3,), ()), ((10, 11), ()), ((12, 13, 14), ())]),
+])
+def test_plain_and_streaming_accesses(stream, prec, dims, gates):
+    """Registers on both sides of the sizes where gates change between streaming and plain accesses, on
+    every kernel; against the same contractions in complex128. The tolerances are those of the gates."""
+    import torch
+    D = O.register_size(dims)
+    dt = torch.complex128 if prec == Q.QD_C128 else torch.complex64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    buf = torch.randn(D, dtype=dt, device="cuda", generator=g) / D ** 0.5
+    ref = buf.to(torch.complex128)
+    torch.cuda.synchronize()
+    rng = C.seeded_rng(96)
+    s = Q.qd_state_wrap(dims, prec, buf.data_ptr(), D * buf.element_size(), stream)
+    try:
+        for t, c in gates:
+            dT = int(np.prod([dims[q] for q in t]))
+            U = C.haar_unitary(dT, rng)
+            if t == (2,):
+                U = np.diag(np.exp(1j * rng.uniform(0, 6, dT)))
+            Q.qd_apply_gate_ex(s, t, c, tuple(dims[q] - 1 for q in c), U, Q.QD_FLAG_SKIP_UNITARY_CHECK)
+            Q.qd_state_sync(s)
+            part, left = ref.view(dims), list(range(len(dims)))
+            for q in sorted(c, reverse=True):
+                part = part.select(left.index(q), dims[q] - 1)
+                left.remove(q)
+            m = part.permute([left.index(q) for q in t] + [i for i, q in enumerate(left) if q not in t])
+            m.copy_((torch.as_tensor(U, device="cuda") @ m.reshape(dT, -1)).reshape(m.shape))
+            err = float((buf.to(torch.complex128) - ref).abs().max())
+            assert err <= (1e-12 if prec == Q.QD_C128 else c64_tol(len(gates), 27)), (t, c, err)
+    finally:
+        Q.qd_state_free(s)
