@@ -1133,9 +1133,47 @@ static int variant_of(int B) { return B <= 32 ? 0 : (B <= 64 ? 1 : (B <= 81 ? 2 
 static int variant_kpad(int v) { return v == 0 ? 64 : (v == 1 ? 128 : (v <= 3 ? 192 : 256)); }
 static int variant_ntiles(int v) { return (v == 2 || v == 3) ? 6 : 4; }
 
+// Blocks that the plain FP32 gate kernels apply instead, as one dense gate on the window. A tile of the
+// kernels here is 2B rows of NT columns in KPAD x 16 NTILES: a share B NT / (32 MTW * 16 NTILES) of the
+// matrix cores' work and of each LDS buffer is of use, while the plain kernels do B multiply-adds an
+// amplitude (times of one block, of the state's own traffic in brackets):
+//   B <= 9: one slice per thread always wins: B = 9 of 3^17 2700 -> 370 to 470 us (314), in BF16x3
+//     1420 to 1500; B = 3 8090 -> 382; B = 8 of 2^26 683 (BF16x3 395) -> 185 (163). The gate rides in the
+//     kernel's arguments, so a captured graph holds all of it.
+//   10 <= B <= 64 with a share below 0.4: k_slices_direct_lu and k_dense_mfma, which read the matrix from
+//     the state's parameter ring and so stay out of captures and of registers too small to hide the copy:
+//     B = 27 of 3^17 (0.36) 974 to 1072 -> 577 to 760, B = 12 over the 5.4e7 hybrid register 1250 -> 155,
+//     B = 27 615 -> 255; at 0.42 (B = 16 or 18 there) 350 against 320 to 420. In BF16x3 the kernels here
+//     are bound by their copies, and windows that reach into the runs halve those (B = 27, window end
+//     included, 664 -> 735), so only windows above the runs change over (1003 -> 760, 457 -> 255).
+//   B = 12 and 16 where k_slices_direct_lu takes them: 372 (BF16x3 244) -> 195 us on 4^13 and 2^26.
+static bool plain_block(const qd_state* s, const FusedArgs& a, const FusedBlockDev& d, bool bf, GatePlan* p) {
+  const int B = d.info.B;
+  bool plain = B <= 9;
+  if (!plain && B <= 64 && s->reg.D >= (int64_t(1) << 22)) {
+    const double share = double(B) * a.NT / (0.5 * variant_kpad(d.variant) * 16.0 * variant_ntiles(d.variant));
+    plain = share < 0.4 && (!bf || a.high_window);
+    if (B == 12 || B == 16) {
+      int64_t tmin = INT64_MAX;
+      for (int j = 0; j < d.info.k; ++j) tmin = std::min<int64_t>(tmin, s->reg.strides[d.info.window[j]]);
+      plain = plain || tmin >= tune().run_min;
+    }
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (plain && (hipStreamIsCapturing(s->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) plain = false;
+  }
+  if (!plain) return false;
+  make_plan(s->reg, d.info.window, d.info.k, nullptr, nullptr, 0, d.host64.data(), p);
+  p->cls = QD_CLASS_DENSE;   // as on the matrix cores: zeros of the block are entries like any other
+  p->dst.clear();
+  p->ph.clear();
+  return true;
+}
+
 int launch_fused_block(qd_state* s, const qd_fused* f, int b, int mode) {
   const FusedBlockDev& d = f->dev[b];
   if (!d.geom_ok) return fail(QD_EINVAL, "fused block has no matrix-core tiling");
+  GatePlan plain;
+  if (plain_block(s, d.args, d, mode == QD_MODE_BF16X3_MFMA, &plain)) return launch_gate(s, plain);
   FusedArgs a = d.args;
   a.psi = reinterpret_cast<float2*>(s->data);
   if (a.tiles.count == 0) return QD_OK;

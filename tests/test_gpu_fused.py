@@ -392,3 +392,77 @@ def test_kernel_instances_by_block_shape(stream, dims, window, k32, kbf, exact):
             assert_gate(ref, psi, (dims, window, want))
     finally:
         Q.qd_fused_free(f)
+
+
+@pytest.mark.parametrize("dims, window, k32, kbf", [
+    ((3,) * 6, (2,), "k_slices_direct", "k_slices_direct"),                     # B = 3
+    ((2, 3, 2, 3, 4), (3,), "k_slices_tiled", "k_slices_tiled"),
+    ((2, 3, 2, 3, 4, 3), (0, 4), "k_slices_tiled", "k_slices_tiled"),           # 8
+    ((3,) * 6, (0, 1), "k_slices_direct", "k_slices_direct"),                   # 9: the last that always goes there
+    ((2, 5, 3, 2, 3), (0, 1), "k_fused_rows<1", "k_fused_rows<1"),              # 10, a small register
+    ((3,) * 14, (0, 1, 2), "k_dense_mfma<float>", "k_dense_mfma<float>"),       # 27: 27 of 64 columns, 27 of 32 rows
+    ((3,) * 14, (0, 1, 13), "k_dense_mfma<float>", "k_fused_rows<1"),           # the window reaches into the runs
+    ((2,) * 22, (3, 5, 7, 9), "k_slices_direct_lu<float, 16>", "k_slices_direct_lu<float, 16>"),
+    ((2,) * 22, (3, 5, 7, 9, 11), "k_fused_rows<1", "k_fused_rows<1"),          # 32
+])
+def test_small_blocks_by_the_gate_kernels(stream, dims, window, k32, kbf):
+    """Blocks that would leave the matrix-core tiles mostly padding run on the plain FP32 gate kernels;
+    both modes meet the FP32 bound there, 4 (2B) 2^-24 of the 2-norm (BF16x3 blocks that stay: 2^-15)."""
+    import torch
+    rng = C.seeded_rng(sum(dims) * 37 + len(window))
+    B = int(np.prod([dims[q] for q in window]))
+    D = int(np.prod(dims))
+    U = C.haar_unitary(B, rng)
+    f = fuse(C.Circuit(tuple(dims), [C.Gate("U", tuple(window), U=U)]), max(B, 2), stream)
+    psi0 = rng.standard_normal(D) + 1j * rng.standard_normal(D)
+    psi0 = (psi0 / np.linalg.norm(psi0)).astype(np.complex64)
+    ref = O.apply_gate(psi0.astype(np.complex128), dims, window, (), (), U)
+    try:
+        for mode, want in ((Q.QD_MODE_FP32_MFMA, k32), (Q.QD_MODE_BF16X3_MFMA, kbf)):
+            s = Q.qd_state_init(dims, Q.QD_C64, stream)
+            try:
+                Q.qd_state_upload(s, psi0)
+                Q.qd_apply_fused(s, f, mode)
+                assert Q.qd_last_kernel().startswith(want), (mode, Q.qd_last_kernel())
+                psi = Q.qd_state_download(s)
+            finally:
+                Q.qd_state_free(s)
+            bf = mode == Q.QD_MODE_BF16X3_MFMA and want.startswith("k_fused")
+            assert np.linalg.norm(psi - ref) <= (2.0 ** -15 if bf else 8 * B * 2.0 ** -24), (mode, want)
+    finally:
+        Q.qd_fused_free(f)
+
+
+def test_small_blocks_under_capture():
+    """While a stream is captured, blocks whose matrix a gate kernel would read from a buffer that later
+    calls write again keep the matrix-core kernels; those whose matrix rides in the kernel's arguments do
+    not. Every replay equals the eager run."""
+    import torch
+    dims = (3,) * 14
+    rng = C.seeded_rng(98)
+    gates = [C.Gate("U", w, U=C.haar_unitary(3 ** len(w), rng)) for w in ((4, 5), (0, 1, 2))]
+    st = torch.cuda.Stream()
+    fs = [fuse(C.Circuit(dims, [g]), 27, st.cuda_stream) for g in gates]
+    s, t = Q.qd_state_init(dims, Q.QD_C64, st.cuda_stream), Q.qd_state_init(dims, Q.QD_C64, st.cuda_stream)
+    graph = torch.cuda.CUDAGraph()
+    names = []
+    try:
+        with torch.cuda.graph(graph, stream=st):
+            for f in fs:
+                Q.qd_apply_fused(s, f, Q.QD_MODE_FP32_MFMA)
+                names.append(Q.qd_last_kernel())
+        assert names[0].startswith("k_slices_direct") and names[1].startswith("k_fused_rows"), names
+        for _ in range(3):
+            for h in (s, t):
+                Q.qd_state_set_basis(h, (1,) * 14)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for f in fs:
+                Q.qd_apply_fused(t, f, Q.QD_MODE_FP32_MFMA)
+            assert max_abs(Q.qd_state_download(s), Q.qd_state_download(t)) <= 8 * 27 * 2.0 ** -24
+    finally:
+        for h in (s, t):
+            Q.qd_state_free(h)
+        for f in fs:
+            Q.qd_fused_free(f)
