@@ -238,6 +238,15 @@ def _dptr(a: np.ndarray):
     return a.ctypes.data_as(_DP)
 
 
+def _dref(a: np.ndarray):
+    """_dptr for the arguments of a call: a reference taken through the buffer protocol, 0.9 us where
+    data_as takes 4.5 (a read-only or an empty array has no writable buffer to refer to)."""
+    try:
+        return C.byref(C.c_double.from_buffer(a))
+    except (TypeError, ValueError):
+        return _dptr(a)
+
+
 # ------------------------------------------------------------------------------ library, register
 def qd_version() -> str:
     return load().qd_version().decode()
@@ -327,9 +336,14 @@ def qd_state_dims(s: int):
 
 
 def _check_shape(dims, targets, Uc):
-    if not len(targets) or any(not 0 <= int(t) < len(dims) for t in targets):
-        return  # the library reports the bad target list
-    dT = int(np.prod([dims[int(t)] for t in targets]))
+    n, dT = len(dims), 1
+    for t in targets:
+        t = int(t)
+        if not 0 <= t < n:
+            return  # the library reports the bad target list
+        dT *= int(dims[t])
+    if not len(targets):
+        return
     if Uc.shape != (dT, dT):
         raise QDError(QD_EDIM, f"U has shape {Uc.shape}, the targets need ({dT}, {dT})")
 
@@ -377,14 +391,14 @@ def qd_apply_gate(s: int, targets, controls, control_values, U):
     Uc = _cplx(U)
     _check_shape(qd_state_dims(s), targets, Uc)
     _check(load().qd_apply_gate(_P(s), _i32(targets), len(targets), _i32(controls), _i32(control_values),
-                                len(controls), _dptr(Uc)))
+                                len(controls), _dref(Uc)))
 
 
 def qd_apply_gate_ex(s: int, targets, controls, control_values, U, flags: int):
     Uc = _cplx(U)
     _check_shape(qd_state_dims(s), targets, Uc)
     _check(load().qd_apply_gate_ex(_P(s), _i32(targets), len(targets), _i32(controls), _i32(control_values),
-                                   len(controls), _dptr(Uc), flags))
+                                   len(controls), _dref(Uc), flags))
 
 
 _KIND = {"X": QD_GATE_X, "Z": QD_GATE_Z, "F": QD_GATE_F}

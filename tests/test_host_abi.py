@@ -442,3 +442,33 @@ def test_batch_tuning_keys(tmp_path):
     finally:
         for k, v in enumerate(keep):
             Q.qd_batch_tune_key_set(k, v)
+
+
+@pytest.mark.parametrize("n", [15, 16, 17, 24, 35, 81])
+def test_unitarity_limit_of_larger_gates(n):
+    """max |(U^dag U)_ij - delta_ij| <= 1e-10 decides, whatever the size (15: column by column, from 16 in
+    panels of eight), for each kind of entry and wherever it lies: just inside is accepted, just outside
+    refused, and so are NaN and Inf anywhere."""
+    rng = np.random.default_rng(n)
+    z = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))
+    U = np.ascontiguousarray(np.linalg.qr(z)[0])
+
+    def verdict(V):
+        rc = Q.qd_validate_gate((n,), (0,), (), (), V)
+        assert rc in (Q.QD_OK, Q.QD_ENOTUNITARY)
+        return rc == Q.QD_OK
+
+    assert verdict(U)
+    places = [(0, 0), (0, n - 1), (n - 1, n - 1), (n // 2, n - 1), (7, 8), (n - 2, n - 1)]
+    for i, j in places:
+        for eps, ok in ((0.98e-10, True), (1.02e-10, False)):
+            V = U.copy()
+            if i == j:
+                V[:, i] *= 1 + eps / 2                  # |column|^2 - 1 = eps
+            else:
+                V[:, j] += eps * 1j * U[:, i]           # <column i, column j> = i eps
+            assert verdict(V) is ok, (i, j, eps)
+        for bad in (np.nan, np.inf, complex(0, np.nan), complex(0, -np.inf)):
+            V = U.copy()
+            V[i, j] = bad
+            assert not verdict(V)
