@@ -75,7 +75,10 @@ struct FusedBlockDev {
 int plan_fusion(const Register& r, const qd_gate* gates, int32_t g, int32_t max_block,
                 std::vector<int32_t>* block_of, std::vector<FusedBlockInfo>* blocks);
 int launch_fused_block(qd_state* s, const struct ::qd_fused* f, int b, int mode);
-int fused_geometry(const Register& r, FusedBlockDev* d);
+int fused_geometry(const Register& r, FusedBlockDev* d, std::vector<char>* image);
+void fused_bind(FusedBlockDev* d, char* base);
+// appends to the image of a fused circuit's uploaded memory, on a 256-byte boundary; returns where
+size_t fused_stage(std::vector<char>* image, const void* src, size_t bytes);
 int fused_kpad(int B);            // leading dimension of the real embedding for block dimension B
 
 }  // namespace qd
@@ -84,4 +87,5 @@ struct qd_fused {
   qd::Register reg;
   hipStream_t stream = nullptr;
   std::vector<qd::FusedBlockDev> dev;
+  char* arena = nullptr;            // one device allocation: everything the blocks point to
 };

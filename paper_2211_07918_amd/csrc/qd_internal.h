@@ -125,6 +125,7 @@ struct ParamRing {            // pinned host staging + device copy for per-call 
   size_t cap = 0;
   size_t head = 0;
   size_t first = size_t(8) << 20;   // capacity it starts with
+  bool lent = false;                // the buffers belong to someone else, who frees them
 };
 
 }  // namespace qd

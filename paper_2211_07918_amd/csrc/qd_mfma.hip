@@ -1221,7 +1221,14 @@ int fused_kpad(int B) { return variant_kpad(variant_of(B)); }
 
 // Tile geometry of a block on its register: the low suffix L = {pq..n-1} grows from the least
 // significant qudit while the non-window part of L (the columns of a tile) stays within ntmax.
-int fused_geometry(const Register& r, FusedBlockDev* d) {
+// The tables are appended to *image; the block's pointers hold offsets into it until fused_bind.
+int fused_geometry(const Register& r, FusedBlockDev* d, std::vector<char>* image) {
+  auto stage = [&](auto** out, const auto& v) {
+    using T = typename std::remove_reference<decltype(**out)>::type;
+    static_assert(sizeof(T) == sizeof(v[0]), "table type");
+    const size_t at = fused_stage(image, v.data(), v.size() * sizeof(T));
+    *out = reinterpret_cast<T*>(at);
+  };
   const FusedBlockInfo& in = d->info;
   const int B = in.B;
   d->variant = variant_of(B);
@@ -1328,15 +1335,9 @@ int fused_geometry(const Register& r, FusedBlockDev* d) {
         }
       }
   }
-  QD_HIP(hipMalloc((void**)&d->tab_rowpos, sizeof(int32_t) * RY));
-  QD_HIP(hipMalloc((void**)&d->tab_colpos, sizeof(int32_t) * NC));
-  QD_HIP(hipMemcpy(d->tab_rowpos, rowpos.data(), sizeof(int32_t) * RY, hipMemcpyHostToDevice));
-  QD_HIP(hipMemcpy(d->tab_colpos, colpos.data(), sizeof(int32_t) * NC, hipMemcpyHostToDevice));
-  QD_HIP(hipMalloc((void**)&d->tab_wrow, sizeof(uint32_t) * RY));
-  QD_HIP(hipMemcpy(d->tab_wrow, wrow.data(), sizeof(uint32_t) * RY, hipMemcpyHostToDevice));
-  a.wrow = d->tab_wrow;
-  a.rowpos = d->variant <= 3 ? d->tab_rowpos : nullptr;
-  a.colpos = d->tab_colpos;
+  stage(&d->tab_rowpos, rowpos);
+  stage(&d->tab_colpos, colpos);
+  stage(&d->tab_wrow, wrow);
   // tile moves in 16-byte units: an odd run length keeps BL + 1 LDS slots per run, the run starting
   // at slot (tile origin + run offset) & 1, so the row table depends on the origin's parity
   if ((BL & 1u) == 0) {
@@ -1355,25 +1356,36 @@ int fused_geometry(const Register& r, FusedBlockDev* d) {
         const int32_t shift = int32_t((uint64_t(par) + uint64_t(hoff[h])) & 1u);
         rp2[size_t(par) * RY + y] = int32_t(h * (BL + 1) + lo) + shift;
       }
-    QD_HIP(hipMalloc((void**)&d->tab_rowpos_odd, sizeof(int32_t) * 2 * RY));
-    QD_HIP(hipMemcpy(d->tab_rowpos_odd, rp2.data(), sizeof(int32_t) * 2 * RY, hipMemcpyHostToDevice));
-    if (d->variant <= 3) a.rowpos = d->tab_rowpos_odd;
+    stage(&d->tab_rowpos_odd, rp2);
   }
   a.upm = make_magic32(a.upr);
-  QD_HIP(hipMalloc((void**)&d->tab_hoff, sizeof(int64_t) * dH));
-  QD_HIP(hipMalloc((void**)&d->tab_yh, sizeof(int32_t) * dH));
-  QD_HIP(hipMalloc((void**)&d->tab_lmap, sizeof(uint32_t) * BL));
-  QD_HIP(hipMemcpy(d->tab_hoff, hoff.data(), sizeof(int64_t) * dH, hipMemcpyHostToDevice));
-  QD_HIP(hipMemcpy(d->tab_yh, yh.data(), sizeof(int32_t) * dH, hipMemcpyHostToDevice));
-  QD_HIP(hipMemcpy(d->tab_lmap, lmap.data(), sizeof(uint32_t) * BL, hipMemcpyHostToDevice));
+  stage(&d->tab_hoff, hoff);
+  stage(&d->tab_yh, yh);
+  stage(&d->tab_lmap, lmap);
+  d->geom_ok = true;
+  return QD_OK;
+}
+
+// Turns the offsets of a block's tables into addresses, base being where the image lies on the device.
+void fused_bind(FusedBlockDev* d, char* base) {
+  auto at = [&](auto*& p) { p = reinterpret_cast<typename std::remove_reference<decltype(p)>::type>(base + reinterpret_cast<size_t>(p)); };
+  FusedArgs& a = d->args;
+  at(d->tab_rowpos);
+  at(d->tab_colpos);
+  at(d->tab_wrow);
+  at(d->tab_hoff);
+  at(d->tab_yh);
+  at(d->tab_lmap);
+  if (a.fill == 1) at(d->tab_rowpos_odd);
+  a.wrow = d->tab_wrow;
+  a.rowpos = d->variant > 3 ? nullptr : a.fill == 1 ? d->tab_rowpos_odd : d->tab_rowpos;
+  a.colpos = d->tab_colpos;
   a.hoff = d->tab_hoff;
   a.yh = d->tab_yh;
   a.lmap = d->tab_lmap;
   a.a32 = d->a32;
   a.ahi = reinterpret_cast<const __bf16*>(d->ahi);
   a.alo = reinterpret_cast<const __bf16*>(d->alo);
-  d->geom_ok = true;
-  return QD_OK;
 }
 
 }  // namespace qd

@@ -445,8 +445,9 @@ int ring_push(qd_state* s, const void* src, size_t bytes, void** dev_out) {
 }
 
 void ring_free(ParamRing* r) {
-  if (r->host) (void)hipHostFree(r->host);
-  if (r->dev) (void)hipFree(r->dev);
+  if (r->host && !r->lent) (void)hipHostFree(r->host);
+  if (r->dev && !r->lent) (void)hipFree(r->dev);
+  r->lent = false;
   r->host = r->dev = nullptr;
   r->cap = r->head = 0;
 }
