@@ -203,7 +203,7 @@ int qd_fuse(const int32_t* dims, int32_t n, const qd_gate* gates, int32_t g, int
   // blocks, each the identity; the tables of their tilings; the jobs of k_embed), the parameter ring of
   // the gates that build them, and the real embeddings. The blocks are built one after the other on the
   // stream, come back in one copy, and the call waits once. With an allocation, a copy and a wait for each
-  // table and block, a QFT on ten ququarts in 11 blocks took 1.82 ms of host time; now 0.32.
+  // table and block, 60 gates on 15 qudits in 11 blocks took 1.82 ms of host time; now 0.32.
   std::vector<char> image;
   std::vector<size_t> u_at(nb), a_at(nb);
   for (size_t b = 0; b < nb; ++b) {
