@@ -184,3 +184,16 @@ def test_hybrid_20_qudits_full_size(stream):
             assert np.allclose(a, b, rtol=1e-12, atol=1e-300)
     finally:
         Q.qd_state_free(s)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("dims", [(9, 7), (4, 16), (5, 13), (3, 5, 17), (4, 4, 16), (4, 4, 4, 4, 3, 3, 3), (3,) * 12,
+                                  (2, 11, 13, 17, 19, 3), (4,) * 11])
+def test_chunk_sums_four_at_a_time(stream, dims, prec):
+    """Chunk sums are made four at a time by one wavefront, each lane ending with one of them: registers
+    of fewer chunks than that, ragged last chunks, and grids that go round more than once; all exact."""
+    s, held = upload(dims, random_state(dims, 77 + sum(dims), 0.3), prec, stream)
+    try:
+        check_all(s, held, dims, shots=4000, seed=5, eps_list=(0.0, 0.5 / np.prod(dims)))
+    finally:
+        Q.qd_state_free(s)
