@@ -1173,7 +1173,10 @@ int launch_fused_block(qd_state* s, const qd_fused* f, int b, int mode) {
   const FusedBlockDev& d = f->dev[b];
   if (!d.geom_ok) return fail(QD_EINVAL, "fused block has no matrix-core tiling");
   GatePlan plain;
-  if (plain_block(s, d.args, d, mode == QD_MODE_BF16X3_MFMA, &plain)) return launch_gate(s, plain);
+  if (plain_block(s, d.args, d, mode == QD_MODE_BF16X3_MFMA, &plain)) {
+    const int rc = launch_gate(s, plain);
+    if (rc != QD_ENOMEM) return rc;   // no room for the state's parameter buffer: the kernels here need none
+  }
   FusedArgs a = d.args;
   a.psi = reinterpret_cast<float2*>(s->data);
   if (a.tiles.count == 0) return QD_OK;

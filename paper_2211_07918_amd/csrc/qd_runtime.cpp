@@ -411,8 +411,13 @@ int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out
     }
     r->cap = r->first;
     while (r->cap < need) r->cap *= 2;
-    QD_HIP(hipHostMalloc((void**)&r->host, r->cap, hipHostMallocDefault));
-    QD_HIP(hipMalloc((void**)&r->dev, r->cap));
+    hipError_t e = hipHostMalloc((void**)&r->host, r->cap, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipMalloc((void**)&r->dev, r->cap);
+    if (e != hipSuccess) {   // none of it is kept: the next call tries both again
+      (void)hipGetLastError();
+      ring_free(r);
+      return hip_fail(e, "parameter buffer");
+    }
     r->head = 0;
   }
   if (r->head + need > r->cap) {

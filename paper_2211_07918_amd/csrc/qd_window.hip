@@ -491,7 +491,7 @@ using namespace win;
 // Applies the gates in order (up to exchanges of neighbours that commute exactly: no qudit in common
 // that either of them changes). Gates run one by one, as qd_apply_gate launches them, on registers of
 // 2^32 amplitudes or more, while the stream is captured (a group's tables are uploaded from a buffer
-// that later calls write again) and where the costs above say so.
+// that later calls write again), where the costs above say so and where the buffer cannot be allocated.
 int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
   const Register& r = s->reg;
   const size_t n = list.size();
@@ -572,6 +572,11 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
     std::memcpy(blob.data() + at, p, bytes_);
     return at;
   };
+  auto one_by_one = [&](const Pass& ps) -> int {
+    int rc = QD_OK;
+    for (size_t i = 0; i < ps.gates.size() && !rc; ++i) rc = alone(size_t(ps.gates[i]));
+    return rc;
+  };
   for (const Pass& ps : passes) {
     bool ok = ps.window != 0;
     Args a;
@@ -593,10 +598,8 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
         ok = build_op(r, gate[size_t(ps.gates[i])], ps.window, order, lst, amp, ps.E, &digits, &ops[i], &rest[i], &tab);
     }
     if (!ok) {
-      for (int g : ps.gates) {
-        int rc = alone(size_t(g));
-        if (rc) return rc;
-      }
+      int rc = one_by_one(ps);
+      if (rc) return rc;
       continue;
     }
     hoff.resize(nh);
@@ -628,6 +631,11 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
     blob.resize((blob.size() + 63) & ~size_t(63));   // the last line is touched whole
     char *host = nullptr, *dev = nullptr;
     int rc = ring_reserve(&s->ring, s->stream, blob.size(), &host, &dev);
+    if (rc == QD_ENOMEM) {   // no room for the tables: gates one by one need none
+      rc = one_by_one(ps);
+      if (rc) return rc;
+      continue;
+    }
     if (rc) return rc;
     std::memcpy(host, blob.data(), blob.size());
     rc = ring_commit(&s->ring, s->stream, host, dev, blob.size());
