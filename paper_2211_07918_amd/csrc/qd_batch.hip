@@ -660,7 +660,7 @@ static int apply_layer_t(qd_batch* b, const std::vector<BatchOp>& ops) {
   }
   // recording: the layer's parameters live in their own device buffer for the graph's lifetime
   void* buf = nullptr;
-  QD_HIP(hipMalloc(&buf, blob.size()));
+  QD_HIP(dev_malloc(&buf, blob.size()));
   b->layer_bufs.push_back(buf);
   QD_HIP(hipMemcpy(buf, blob.data(), blob.size(), hipMemcpyHostToDevice));
   rc = compose(static_cast<unsigned char*>(buf));   // once, at recording: replays reuse the blocks
@@ -717,8 +717,8 @@ int qd_batch_create(int32_t nc, const int32_t* n_per, const int32_t* dims_flat, 
   }
   b->total = total;
   const size_t bytes = size_t(total) * amp_bytes(prec);
-  hipError_t e = hipMalloc(&b->arena, bytes);
-  if (e == hipSuccess) e = hipMalloc((void**)&b->offs_dev, sizeof(int64_t) * nc);
+  hipError_t e = dev_malloc(&b->arena, bytes);
+  if (e == hipSuccess) e = dev_malloc((void**)&b->offs_dev, sizeof(int64_t) * nc);
   if (e == hipSuccess) e = hipMemcpy(b->offs_dev, b->offs.data(), sizeof(int64_t) * nc, hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     qd_batch_free(b);
@@ -825,7 +825,7 @@ int qd_batch_autotune(qd_batch* b, const qd_gate* gates) {
   // the arena is saved and restored around the timed layers
   const size_t bytes = size_t(b->total) * amp_bytes(b->prec);
   void* save = nullptr;
-  QD_HIP(hipMalloc(&save, bytes));
+  QD_HIP(dev_malloc(&save, bytes));
   hipError_t e = hipMemcpyAsync(save, b->arena, bytes, hipMemcpyDeviceToDevice, b->stream);
   TuneParams& tp = tune();
   const int old_block = tp.batch_block, old_spt = tp.batch_spt, old_wpc = tp.batch_wpc;
@@ -924,7 +924,7 @@ int qd_batch_autotune_layers(qd_batch* b, const qd_gate* gates, int32_t nlayers)
   if (b->capturing) return fail(QD_EINVAL, "cannot tune while recording");
   const size_t bytes = size_t(b->total) * amp_bytes(b->prec);
   void* save = nullptr;
-  QD_HIP(hipMalloc(&save, bytes));
+  QD_HIP(dev_malloc(&save, bytes));
   hipError_t e = hipMemcpyAsync(save, b->arena, bytes, hipMemcpyDeviceToDevice, b->stream);
   // each width is recorded into a graph of the tuner's own (the composition on the host happens
   // while recording, outside the timed replays); the caller's recorded graph is put aside meanwhile

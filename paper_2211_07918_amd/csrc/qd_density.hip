@@ -590,7 +590,7 @@ int qd_density_trace(qd_state* rho, double* re, double* im) {
   const uint64_t Dp = uint64_t(phys.D);
   const unsigned g = red_grid(Dp);
   double* part = nullptr;
-  QD_HIP(hipMalloc((void**)&part, size_t(g) * 2 * sizeof(double)));
+  QD_HIP(dev_malloc((void**)&part, size_t(g) * 2 * sizeof(double)));
   if (rho->prec == QD_C128)
     hipLaunchKernelGGL(k_trace_part<double>, dim3(g), dim3(kBlock), 0, rho->stream, (const double*)rho->data, Dp, part);
   else
@@ -611,7 +611,7 @@ int qd_density_probabilities(qd_state* rho, double* out, int32_t out_is_device) 
   if (rc) return rc;
   const uint64_t D = uint64_t(phys.D);
   double* dst = out;
-  if (!out_is_device) QD_HIP(hipMalloc((void**)&dst, D * sizeof(double)));
+  if (!out_is_device) QD_HIP(dev_malloc((void**)&dst, D * sizeof(double)));
   const dim3 grid(unsigned((D + kBlock - 1) / kBlock));
   if (rho->prec == QD_C128)
     hipLaunchKernelGGL(k_diag<double>, grid, dim3(kBlock), 0, rho->stream, (const double*)rho->data, D, dst);
@@ -644,7 +644,7 @@ int qd_density_fidelity(qd_state* rho, const qd_state* psi, double* out) {
   const uint64_t D = uint64_t(psi->reg.D);
   const unsigned g = unsigned(std::max<uint64_t>(1, std::min<uint64_t>(kRedGrid, D)));
   double* part = nullptr;
-  QD_HIP(hipMalloc((void**)&part, size_t(g) * 2 * sizeof(double)));
+  QD_HIP(dev_malloc((void**)&part, size_t(g) * 2 * sizeof(double)));
   if (rho->prec == QD_C128)
     hipLaunchKernelGGL(k_fidelity_part<double>, dim3(g), dim3(kBlock), 0, rho->stream, (const double*)rho->data,
                        (const double*)psi->data, D, part);

@@ -233,7 +233,7 @@ int qd_fuse(const int32_t* dims, int32_t n, const qd_gate* gates, int32_t g, int
     kmax = std::max(kmax, f->dev[b].Kp);
   }
   if (nb) {
-    hipError_t e = hipMalloc((void**)&f->arena, total);
+    hipError_t e = dev_malloc((void**)&f->arena, total);
     if (e == hipSuccess) e = hipHostMalloc((void**)&pinned, up, hipHostMallocDefault);
     if (e != hipSuccess) return cleanup(hip_fail(e, "fused block allocation"));
     ring.host = pinned + ring_at;

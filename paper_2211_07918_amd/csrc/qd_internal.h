@@ -126,6 +126,8 @@ struct ParamRing {            // pinned host staging + device copy for per-call 
   size_t head = 0;
   size_t first = size_t(8) << 20;   // capacity it starts with
   bool lent = false;                // the buffers belong to someone else, who frees them
+  int device = 0;                   // where dev lies
+  bool recorded = false;            // a graph holds copies from it and kernels that read it
 };
 
 }  // namespace qd
@@ -148,6 +150,9 @@ struct qd_state {
 };
 
 namespace qd {
+
+// hipMalloc; where there is no room, the spare parameter buffers that freed states left are released first
+hipError_t dev_malloc(void** p, size_t bytes);
 
 // Reserve `bytes` in the state's parameter ring, copy `src` there and return the device address.
 // Wrapping around synchronises the stream first so no in-flight copy reads recycled memory.

@@ -445,7 +445,7 @@ int ensure_ws(qd_state* s, size_t bytes, bool* moved = nullptr) {
   }
   s->mws = nullptr;
   s->mws_cap = 0;
-  QD_HIP(hipMalloc(&s->mws, bytes));
+  QD_HIP(dev_malloc(&s->mws, bytes));
   s->mws_cap = bytes;
   return QD_OK;
 }

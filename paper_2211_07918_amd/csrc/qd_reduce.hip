@@ -130,7 +130,7 @@ static int ensure_red(qd_state* s, size_t doubles) {
   if (s->red) (void)hipFree(s->red);
   s->red = nullptr;
   s->red_cap = 0;
-  QD_HIP(hipMalloc((void**)&s->red, doubles * sizeof(double)));
+  QD_HIP(dev_malloc((void**)&s->red, doubles * sizeof(double)));
   s->red_cap = doubles;
   return QD_OK;
 }

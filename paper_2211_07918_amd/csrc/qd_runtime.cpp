@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -400,9 +401,86 @@ void fill_slicemap64(const std::vector<Group>& g, int64_t base, SliceMap64* sm) 
 }
 
 // ------------------------------------------------------------------------------------------ param ring
+// Parameter buffers of the usual size that freed states leave to the next ones. Allocating and releasing
+// one takes 26 us (8 MB device and pinned), more than a short circuit on a small register: a state made,
+// two or three gates applied, the norm read and the state freed took 40 us without a buffer, 71 with one of
+// its own. At most kSpareRings are kept, and an allocation that finds no room gets them back.
+constexpr size_t kRingBytes = ParamRing().first;
+constexpr size_t kSpareRings = 4;
+struct SpareRing {
+  int device;
+  char* host;
+  char* dev;
+};
+struct SpareRings {
+  std::mutex mu;
+  std::vector<SpareRing> list;
+};
+static SpareRings& spare_rings() {
+  static SpareRings* s = new SpareRings;   // not destroyed: a state may be freed while the process ends
+  return *s;
+}
+
+static bool take_spare(ParamRing* r) {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return false;
+  SpareRings& s = spare_rings();
+  std::lock_guard<std::mutex> lock(s.mu);
+  for (size_t i = s.list.size(); i-- > 0;)
+    if (s.list[i].device == device) {
+      r->host = s.list[i].host;
+      r->dev = s.list[i].dev;
+      r->device = device;
+      s.list.erase(s.list.begin() + ptrdiff_t(i));
+      return true;
+    }
+  return false;
+}
+
+static bool drop_spares() {
+  SpareRings& s = spare_rings();
+  std::lock_guard<std::mutex> lock(s.mu);
+  for (const SpareRing& x : s.list) {
+    (void)hipHostFree(x.host);
+    (void)hipFree(x.dev);
+  }
+  const bool any = !s.list.empty();
+  s.list.clear();
+  return any;
+}
+
+hipError_t dev_malloc(void** p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory && drop_spares()) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
+// Gives a ring's buffers back; the stream has finished with them.
+static void ring_leave(ParamRing* r) {
+  if (r->host && r->dev && !r->lent && r->cap == kRingBytes) {
+    SpareRings& s = spare_rings();
+    std::lock_guard<std::mutex> lock(s.mu);
+    if (s.list.size() < kSpareRings) {
+      s.list.push_back(SpareRing{r->device, r->host, r->dev});
+      r->host = r->dev = nullptr;
+      r->cap = r->head = 0;
+      return;
+    }
+  }
+  ring_free(r);
+}
+
 int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out, char** dev_out) {
   const size_t align = 256;
   const size_t need = (bytes + align - 1) / align * align;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    r->recorded = true;
+  }
   if (!r->host || need > r->cap) {
     if (r->host) {
       // earlier copies and the kernels reading them must finish before the buffers go away
@@ -411,8 +489,12 @@ int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out
     }
     r->cap = r->first;
     while (r->cap < need) r->cap *= 2;
-    hipError_t e = hipHostMalloc((void**)&r->host, r->cap, hipHostMallocDefault);
-    if (e == hipSuccess) e = hipMalloc((void**)&r->dev, r->cap);
+    hipError_t e = hipSuccess;
+    if (r->cap != kRingBytes || !take_spare(r)) {
+      e = hipGetDevice(&r->device);
+      if (e == hipSuccess) e = hipHostMalloc((void**)&r->host, r->cap, hipHostMallocDefault);
+      if (e == hipSuccess) e = dev_malloc((void**)&r->dev, r->cap);
+    }
     if (e != hipSuccess) {   // none of it is kept: the next call tries both again
       (void)hipGetLastError();
       ring_free(r);
@@ -519,7 +601,7 @@ int qd_state_init(const int32_t* dims, int32_t n, int32_t prec, void* hip_stream
   // 16 spare bytes: a kernel may read one 16-byte unit that ends past the last amplitude (and never
   // writes it)
   const size_t bytes = size_t(s->reg.D) * amp_bytes(prec) + 16;
-  hipError_t e = hipMalloc(&s->data, bytes);
+  hipError_t e = dev_malloc(&s->data, bytes);
   if (e != hipSuccess) {
     delete s;
     (void)hipGetLastError();
@@ -613,11 +695,12 @@ int qd_state_sync(const qd_state* s) {
 
 void qd_state_free(qd_state* s) {
   if (!s) return;
-  (void)hipStreamSynchronize(s->stream);
+  const bool idle = hipStreamSynchronize(s->stream) == hipSuccess;
   if (s->owned && s->data) (void)hipFree(s->data);
   if (s->red) (void)hipFree(s->red);
   if (s->mws) (void)hipFree(s->mws);
-  ring_free(&s->ring);
+  if (idle && !s->ring.recorded) ring_leave(&s->ring);   // (a graph may run on any stream)
+  else ring_free(&s->ring);
   delete s;
 }
 
@@ -649,7 +732,7 @@ int qd_probabilities(const qd_state* s, double* out, int32_t out_is_device) {
   if (out_is_device) return launch_probabilities(s, out);
   double* dev = nullptr;
   const size_t bytes = size_t(s->reg.D) * sizeof(double);
-  QD_HIP(hipMalloc((void**)&dev, bytes));
+  QD_HIP(dev_malloc((void**)&dev, bytes));
   int rc = launch_probabilities(s, dev);
   if (!rc) {
     hipError_t e = hipMemcpyAsync(out, dev, bytes, hipMemcpyDeviceToHost, s->stream);
@@ -665,7 +748,7 @@ int qd_probabilities_norm2(const qd_state* s, double* out, int32_t out_is_device
   if (out_is_device) return reduce_probabilities_norm2(s, out, norm2);
   double* dev = nullptr;
   const size_t bytes = size_t(s->reg.D) * sizeof(double);
-  QD_HIP(hipMalloc((void**)&dev, bytes));
+  QD_HIP(dev_malloc((void**)&dev, bytes));
   int rc = reduce_probabilities_norm2(s, dev, norm2);
   if (!rc) {
     hipError_t e = hipMemcpyAsync(out, dev, bytes, hipMemcpyDeviceToHost, s->stream);

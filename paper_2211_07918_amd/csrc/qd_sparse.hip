@@ -648,7 +648,7 @@ static int ensure(qd_sparse* s, DevBuf& b, size_t need) {
     b.p = nullptr;
     b.cap = 0;
   }
-  hipError_t e = hipMalloc(&b.p, c * sizeof(T));
+  hipError_t e = dev_malloc(&b.p, c * sizeof(T));
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(QD_ENOMEM, "sparse workspace allocation failed (" + std::to_string(c * sizeof(T)) + " bytes)");
@@ -664,8 +664,8 @@ static T* P(const DevBuf& b) {
 
 static int alloc_lists(qd_sparse* s, int64_t cap) {
   for (int b = 0; b < 2; ++b) {
-    hipError_t e1 = hipMalloc((void**)&s->idx[b], size_t(cap) * sizeof(int64_t));
-    hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&s->amp[b], size_t(cap) * sizeof(double2)) : e1;
+    hipError_t e1 = dev_malloc((void**)&s->idx[b], size_t(cap) * sizeof(int64_t));
+    hipError_t e2 = e1 == hipSuccess ? dev_malloc((void**)&s->amp[b], size_t(cap) * sizeof(double2)) : e1;
     if (e2 != hipSuccess) {
       (void)hipGetLastError();
       return fail(QD_ENOMEM, "sparse list allocation failed (" + std::to_string(cap) + " entries)");
@@ -697,8 +697,8 @@ static int grow_lists(qd_sparse* s, int64_t need, int64_t n) {
   int64_t* ni[2] = {nullptr, nullptr};
   double2* na[2] = {nullptr, nullptr};
   for (int b = 0; b < 2; ++b) {
-    hipError_t e1 = hipMalloc((void**)&ni[b], size_t(cap) * sizeof(int64_t));
-    hipError_t e2 = e1 == hipSuccess ? hipMalloc((void**)&na[b], size_t(cap) * sizeof(double2)) : e1;
+    hipError_t e1 = dev_malloc((void**)&ni[b], size_t(cap) * sizeof(int64_t));
+    hipError_t e2 = e1 == hipSuccess ? dev_malloc((void**)&na[b], size_t(cap) * sizeof(double2)) : e1;
     if (e2 != hipSuccess) {
       (void)hipGetLastError();
       for (int q = 0; q < 2; ++q) {
@@ -1152,7 +1152,7 @@ int qd_sparse_init(const int32_t* dims, int32_t n, int64_t capacity, void* hip_s
     qd_sparse_free(s);
     return rc;
   }
-  if (hipMalloc((void**)&s->misc, kMisc * sizeof(int64_t)) != hipSuccess ||
+  if (dev_malloc((void**)&s->misc, kMisc * sizeof(int64_t)) != hipSuccess ||
       hipHostMalloc((void**)&s->hmisc, kMisc * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     qd_sparse_free(s);
@@ -1291,7 +1291,7 @@ int qd_sparse_norm2(qd_sparse* s, double* out) {
   if (rc) return rc;
   const unsigned grid = unsigned(std::max<int64_t>(1, std::min<int64_t>(1024, (n + kBlock * 8 - 1) / (kBlock * 8))));
   double* part = nullptr;
-  QD_HIP(hipMalloc((void**)&part, grid * sizeof(double)));
+  QD_HIP(dev_malloc((void**)&part, grid * sizeof(double)));
   hipLaunchKernelGGL(k_norm_part, dim3(grid), dim3(kBlock), 0, s->stream, s->misc + kCnt0 + s->cur, s->amp[s->cur], part);
   std::vector<double> h(grid);
   hipError_t e = hipGetLastError();
@@ -1313,7 +1313,7 @@ int qd_sparse_probabilities(qd_sparse* s, double* out, int32_t out_is_device, in
   if (n > cap) return fail(QD_EINVAL, "output array holds fewer entries than the state");
   if (n == 0) return QD_OK;
   double* dst = out;
-  if (!out_is_device) QD_HIP(hipMalloc((void**)&dst, size_t(n) * sizeof(double)));
+  if (!out_is_device) QD_HIP(dev_malloc((void**)&dst, size_t(n) * sizeof(double)));
   hipLaunchKernelGGL(k_probs, dim3(blocks_for(n)), dim3(kBlock), 0, s->stream, s->misc + kCnt0 + s->cur, s->amp[s->cur], dst);
   hipError_t e = hipGetLastError();
   if (!out_is_device) {

@@ -191,3 +191,44 @@ def test_complex64_circuit_leaves_the_bits_of_its_gates(stream, dims, n, control
         Q.qd_state_free(s)
         Q.qd_state_free(one)
         Q.qd_circuit_free(c)
+
+
+def test_states_made_and_freed_by_several_threads():
+    """Freed states leave their parameter buffers to the next ones: four threads, each on a stream of its
+    own, make a state for each of forty circuits, apply it and free the state; every result has the bits of
+    the same circuit on a state of its own."""
+    import threading
+    import torch
+    dims = (3, 2, 4, 3, 2, 3, 2, 3)
+    rng = np.random.default_rng(10)
+    circuits = [named_circuit(dims, 20 + i, rng)[0] for i in range(8)]
+
+    def result(c, stream):
+        s = Q.qd_state_init(dims, Q.QD_C128, stream)
+        try:
+            Q.qd_circuit_apply(s, c)
+            return Q.qd_state_download(s)
+        finally:
+            Q.qd_state_free(s)
+
+    want = [result(c, 0) for c in circuits]
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    wrong, done = [], []
+
+    def work(i):
+        for n in range(40):
+            k = (3 * i + n) % len(circuits)
+            if not np.array_equal(result(circuits[k], streams[i].cuda_stream), want[k]):
+                wrong.append((i, n, k))
+        done.append(i)
+
+    try:
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert not wrong and len(done) == 4, (wrong, done)
+    finally:
+        for c in circuits:
+            Q.qd_circuit_free(c)

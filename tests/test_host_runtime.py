@@ -40,3 +40,44 @@ assert "k_dense_mfma" in launches()[0][0], launches()
 for h in (s, rho, t): Q.qd_state_free(h)
 Q.qd_fused_free(f)
 """)
+
+
+def test_parameter_buffers_pass_from_state_to_state(host_runtime):
+    """A program that makes a state for each circuit does not allocate a parameter buffer for each: freed
+    states leave theirs, a bounded number of them, to the next ones, from any thread; an allocation that
+    finds no room gets the memory back."""
+    host_runtime("""
+import threading
+RING = 8 << 20
+dims = (3, 2, 4, 3, 2, 3, 2, 3)
+c = Q.qd_circuit_create(dims)
+for q in (0, 3, 5, 7, 2): Q.qd_circuit_add(c, Q.QD_GATE_F, q)
+def one():
+    s = Q.qd_state_init(dims, Q.QD_C128, 0)
+    Q.qd_circuit_apply(s, c)
+    return s
+for _ in range(20): Q.qd_state_free(one())
+assert hip.host_made(PINNED) == 1 and hip.host_made(DEVICE) == 21, (hip.host_made(PINNED), hip.host_made(DEVICE))
+many = [one() for _ in range(30)]
+assert hip.host_held(PINNED) == 30 * RING           # one each while they live
+for s in many: Q.qd_state_free(s)
+assert hip.host_held(PINNED) <= 4 * RING and hip.host_held(DEVICE) <= 4 * RING
+def work():
+    for _ in range(200): Q.qd_state_free(one())
+ts = [threading.Thread(target=work) for _ in range(8)]
+for t in ts: t.start()
+for t in ts: t.join()
+assert hip.host_held(PINNED) <= 4 * RING and hip.host_held(DEVICE) <= 4 * RING
+assert hip.host_held(DEVICE) > 0
+hip.host_limit(DEVICE, hip.host_held(DEVICE) + (1 << 20))
+s = Q.qd_state_init((2,) * 20, Q.QD_C128, 0)          # 16 MB: fits without the spare buffers only
+hip.host_limit(DEVICE, -1)
+Q.qd_state_free(s)
+assert hip.host_held(DEVICE) == 0 and hip.host_held(PINNED) == 0
+s = one()                                             # a buffer that a graph has recorded is not passed on
+hip.host_capture(1)
+Q.qd_apply_gate_ex(s, (1, 3, 5), (), (), np.linalg.qr(np.random.default_rng(1).standard_normal((18, 18)))[0], 1)
+hip.host_capture(0)
+Q.qd_state_free(s)
+assert hip.host_held(DEVICE) == 0 and hip.host_held(PINNED) == 0
+""")
