@@ -308,8 +308,11 @@ int qd_fuse(const int32_t* dims, int32_t n, const qd_gate* gates, int32_t g, int
     e = hipMemcpyAsync(pinned, f->arena, u_bytes, hipMemcpyDeviceToHost, f->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(f->stream);
     if (e != hipSuccess) return cleanup(hip_fail(e, "fused block build"));
-    for (size_t b = 0; b < nb; ++b)
-      std::memcpy(f->dev[b].host64.data(), pinned + u_at[b], f->dev[b].host64.size() * sizeof(double));
+    for (size_t b = 0; b < nb; ++b) {
+      FusedBlockDev& d = f->dev[b];
+      std::memcpy(d.host64.data(), pinned + u_at[b], d.host64.size() * sizeof(double));
+      if (d.geom_ok && d.info.B <= 9) fused_plan(r, d, &d.plain);
+    }
   }
   ring_free(&ring);
   if (pinned) (void)hipHostFree(pinned);

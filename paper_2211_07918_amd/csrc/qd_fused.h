@@ -70,6 +70,8 @@ struct FusedBlockDev {
   __hip_bfloat16* ahi = nullptr;    // BF16 split of a32: hi
   __hip_bfloat16* alo = nullptr;    //                    lo
   std::vector<double> host64;       // host copy of u64
+  GatePlan plain;                   // fused_plan of a block of B <= 9, made once (k = 0: none): making it on every
+                                    // call took half of the 0.8 us of host time that such a block took
 };
 
 int plan_fusion(const Register& r, const qd_gate* gates, int32_t g, int32_t max_block,
@@ -79,6 +81,7 @@ int fused_geometry(const Register& r, FusedBlockDev* d, std::vector<char>* image
 void fused_bind(FusedBlockDev* d, char* base);
 // appends to the image of a fused circuit's uploaded memory, on a 256-byte boundary; returns where
 size_t fused_stage(std::vector<char>* image, const void* src, size_t bytes);
+void fused_plan(const Register& r, const FusedBlockDev& d, GatePlan* p);
 int fused_kpad(int B);            // leading dimension of the real embedding for block dimension B
 
 }  // namespace qd

@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <numeric>
@@ -393,6 +394,18 @@ __device__ __forceinline__ Magic32 karg_magic(M* m) {
   return r;
 }
 
+// Bytes [BEGIN, END) of the arguments into the scalar cache, every line asked for at once: read where they are
+// needed they are a chain of misses, which bounds the kernel on small registers (9 x 9 gates on 3^9: 7.9 ->
+// 5.8 us in complex128, 8.7 -> 6.5 in complex64; 3 x 3 on 3^9 4.9 -> 4.3).
+template <uint32_t BEGIN, uint32_t END, typename A>
+__device__ __forceinline__ void warm_lines(A* a) {
+  QD_KARG uint32_t* w = (QD_KARG uint32_t*)a;
+  uint32_t t = w[END / 4 - 1];
+#pragma unroll
+  for (uint32_t i = BEGIN / 4; i < END / 4; i += 16) t ^= w[i];
+  __asm__ volatile("" ::"s"(t));
+}
+
 // Amplitudes a thread moves per tile: the tile holds at most 256 * kTileEpt<R> amplitudes.
 template <typename R> struct TileEpt;
 template <> struct TileEpt<double> { static constexpr int value = 8; };
@@ -406,7 +419,11 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
   using C = typename CxT<R>::T;
   constexpr int EPT = TileEpt<R>::value;
   constexpr bool kDense = DenseDim<OP>::value > 0;
-  QD_KARG TileArgs<R, DT, OP>* a = (QD_KARG TileArgs<R, DT, OP>*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr bool kRows = kDense && DT * sizeof(R) > 24;   // a row of U at a time (all of it would not fit the scalar registers)
+  using Args = TileArgs<R, DT, OP>;
+  QD_KARG Args* a = (QD_KARG Args*)__builtin_amdgcn_kernarg_segment_ptr();
+  const bool cold = blockIdx.x < 1024;   // later workgroups find what their predecessors on the CU have read
+  if (cold) warm_lines<0, offsetof(Args, op)>(a);
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ int64_t s_hoff[kMaxTileRuns];
   C* lds = reinterpret_cast<C*>(lds_raw);
@@ -475,6 +492,10 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
           vi[e] = t.y;
         }
     }
+    if constexpr (kRows) {
+      // U's, while the tile is on its way
+      if (cold) warm_lines<offsetof(Args, op), offsetof(Args, op) + sizeof(OP)>(a);
+    }
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
       const uint32_t idx = tl + e * bs;
@@ -512,8 +533,7 @@ __global__ __launch_bounds__(256) void k_slices_tiled(TileArgs<R, DT, OP>) {
           yv.y = im;
           lds[b + a->toff[r]] = yv;
         };
-        // a row of U at a time (all of it would not fit the scalar registers)
-        if constexpr (DT * sizeof(R) <= 24) {
+        if constexpr (!kRows) {
 #pragma unroll
           for (int r = 0; r < DT; ++r) row(r);
         } else {
@@ -998,6 +1018,9 @@ bool tile_geometry(const Register& r, const GatePlan& p, int prec, TileGeom* g) 
     // (complex128: 648 against 1296 amplitudes 565 and 615 us on the hybrid register of 1.1e8, 1024
     // against 2048 178 and 197 us on 2^25), while tiles below that size leave the workgroups short of
     // loads (243 against 729 amplitudes 384 and 243 us on 3^16; complex64: 729 against 2187 221 and 132 us).
+    // A register of fewer than 192 tiles of that size (of 256 CUs) takes smaller ones, down to one amplitude
+    // a thread: complex64, radix 8 on 2^15 amplitudes 7.2 -> 5.2 us with 64 tiles instead of 8, 9 x 9 gates on
+    // 3^9 6.4 -> 6.0; tiles of 64 amplitudes are slower again (5.7 and 6.1).
     const uint64_t enough = 9216 / amp_bytes(prec);
     while (pq > 0 && BL * dH < enough) {
       const int q = pq - 1;
@@ -1006,6 +1029,7 @@ bool tile_geometry(const Register& r, const GatePlan& p, int prec, TileGeom* g) 
       const uint64_t nBL = drop ? BL : BL * r.dims[q];
       const uint64_t ndH = is_t[q] ? dH / r.dims[q] : dH;
       if (nBL * ndH > emax) break;
+      if (BL * dH >= 256 && nBL * ndH * 192 > uint64_t(r.D)) break;
       pq = q;
       BL = nBL;
       dH = ndH;
@@ -1023,7 +1047,8 @@ bool tile_geometry(const Register& r, const GatePlan& p, int prec, TileGeom* g) 
   return grow(true) || grow(false);
 }
 
-int route_gate(const Register& r, int prec, const GatePlan& p) {
+// The route of a gate; *g is its tile where that is QD_ROUTE_TILED.
+static int route_gate(const Register& r, int prec, const GatePlan& p, TileGeom* g) {
   const bool fast = uint64_t(r.D) <= 0xFFFFFFFFull;
   if (!fast) return QD_ROUTE_GENERIC;
   if (p.cls == QD_CLASS_DIAGONAL && p.dT <= kMaxInlineTable) return QD_ROUTE_DIAG;
@@ -1040,8 +1065,12 @@ int route_gate(const Register& r, int prec, const GatePlan& p) {
     }
     return QD_ROUTE_GEMM;
   }
+  return tile_geometry(r, p, prec, g) ? QD_ROUTE_TILED : QD_ROUTE_DIRECT;
+}
+
+int route_gate(const Register& r, int prec, const GatePlan& p) {
   TileGeom g;
-  return tile_geometry(r, p, prec, &g) ? QD_ROUTE_TILED : QD_ROUTE_DIRECT;
+  return route_gate(r, prec, p, &g);
 }
 
 template <int DT>
@@ -1076,8 +1105,9 @@ static bool streaming(const qd_state* s, const GatePlan& p, uint64_t touched, bo
   return sectors || (s->prec == QD_C128 && lowest > 512);
 }
 
+// tile: the tile of a gate of route QD_ROUTE_TILED, else null
 template <typename R, int DT, typename OP>
-static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
+static int launch_slices(qd_state* s, const GatePlan& p, const OP& op, const TileGeom* tile) {
   const Register& r = s->reg;
   const TuneParams& tp = tune();
   int role[QD_MAX_QUDITS] = {};
@@ -1087,8 +1117,8 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
   int64_t min_stride = INT64_MAX;
   for (int j = 0; j < p.k; ++j) min_stride = std::min<int64_t>(min_stride, r.strides[p.targets[j]]);
   const TuneEntry ent = entry_for(s->prec, min_stride);
-  TileGeom tg;
-  if (tile_geometry(r, p, s->prec, &tg)) {
+  if (tile) {
+    const TileGeom& tg = *tile;
     const int pq = tg.pq;
     const uint64_t BL = tg.BL, dH = tg.dH;
     {
@@ -1285,17 +1315,17 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op) {
 }
 
 template <typename R, int DT>
-static int launch_dense_t(qd_state* s, const GatePlan& p) {
+static int launch_dense_t(qd_state* s, const GatePlan& p, const TileGeom* tile) {
   DenseOp<R, DT> op;
   fill_dense<R, DT>(p, &op);
-  return launch_slices<R, DT>(s, p, op);
+  return launch_slices<R, DT>(s, p, op, tile);
 }
 
 template <typename R, int DT>
-static int launch_mono_t(qd_state* s, const GatePlan& p) {
+static int launch_mono_t(qd_state* s, const GatePlan& p, const TileGeom* tile) {
   MonoOp<R, DT> op;
   fill_mono<R, DT>(p, &op);
-  return launch_slices<R, DT>(s, p, op);
+  return launch_slices<R, DT>(s, p, op, tile);
 }
 
 template <typename R>
@@ -1500,7 +1530,9 @@ static int launch_gemm(qd_state* s, const GatePlan& p) {
 
 template <typename R>
 static int launch_gate_t(qd_state* s, const GatePlan& p) {
-  const int route = route_gate(s->reg, s->prec, p);
+  TileGeom geom;
+  const int route = route_gate(s->reg, s->prec, p, &geom);
+  const TileGeom* tile = route == QD_ROUTE_TILED ? &geom : nullptr;
   // the generic kernel is left with registers of 2^32 amplitudes or more (launch_gemm also hands it
   // gates whose free digits fall into more groups than a slice map holds)
   if (route == QD_ROUTE_GENERIC)
@@ -1513,28 +1545,28 @@ static int launch_gate_t(qd_state* s, const GatePlan& p) {
   // one line 720 -> 575 us), and the zero entries add exact zeros.
   if (p.cls == QD_CLASS_MONOMIAL && !(route == QD_ROUTE_DIRECT && p.dT <= kMaxInlineDense)) {
     switch (p.dT) {
-      case 2: return launch_mono_t<R, 2>(s, p);
-      case 3: return launch_mono_t<R, 3>(s, p);
-      case 4: return launch_mono_t<R, 4>(s, p);
-      case 5: return launch_mono_t<R, 5>(s, p);
-      case 6: return launch_mono_t<R, 6>(s, p);
-      case 7: return launch_mono_t<R, 7>(s, p);
-      case 8: return launch_mono_t<R, 8>(s, p);
-      case 9: return launch_mono_t<R, 9>(s, p);
-      case 12: return launch_mono_t<R, 12>(s, p);
-      case 16: return launch_mono_t<R, 16>(s, p);
+      case 2: return launch_mono_t<R, 2>(s, p, tile);
+      case 3: return launch_mono_t<R, 3>(s, p, tile);
+      case 4: return launch_mono_t<R, 4>(s, p, tile);
+      case 5: return launch_mono_t<R, 5>(s, p, tile);
+      case 6: return launch_mono_t<R, 6>(s, p, tile);
+      case 7: return launch_mono_t<R, 7>(s, p, tile);
+      case 8: return launch_mono_t<R, 8>(s, p, tile);
+      case 9: return launch_mono_t<R, 9>(s, p, tile);
+      case 12: return launch_mono_t<R, 12>(s, p, tile);
+      case 16: return launch_mono_t<R, 16>(s, p, tile);
       default: break;
     }
   }
   switch (p.dT) {
-    case 2: return launch_dense_t<R, 2>(s, p);
-    case 3: return launch_dense_t<R, 3>(s, p);
-    case 4: return launch_dense_t<R, 4>(s, p);
-    case 5: return launch_dense_t<R, 5>(s, p);
-    case 6: return launch_dense_t<R, 6>(s, p);
-    case 7: return launch_dense_t<R, 7>(s, p);
-    case 8: return launch_dense_t<R, 8>(s, p);
-    case 9: return launch_dense_t<R, 9>(s, p);
+    case 2: return launch_dense_t<R, 2>(s, p, tile);
+    case 3: return launch_dense_t<R, 3>(s, p, tile);
+    case 4: return launch_dense_t<R, 4>(s, p, tile);
+    case 5: return launch_dense_t<R, 5>(s, p, tile);
+    case 6: return launch_dense_t<R, 6>(s, p, tile);
+    case 7: return launch_dense_t<R, 7>(s, p, tile);
+    case 8: return launch_dense_t<R, 8>(s, p, tile);
+    case 9: return launch_dense_t<R, 9>(s, p, tile);
     case 12: return launch_direct_lu<R, 12>(s, p);
     case 16: return launch_direct_lu<R, 16>(s, p);
     default: return launch_generic<R>(s, p);

@@ -1137,9 +1137,11 @@ static int variant_ntiles(int v) { return (v == 2 || v == 3) ? 6 : 4; }
 // kernels here is 2B rows of NT columns in KPAD x 16 NTILES: a share B NT / (32 MTW * 16 NTILES) of the
 // matrix cores' work and of each LDS buffer is of use, while the plain kernels do B multiply-adds an
 // amplitude (times of one block, of the state's own traffic in brackets):
-//   B <= 9: one slice per thread always wins: B = 9 of 3^17 2700 -> 370 to 470 us (314), in BF16x3
-//     1420 to 1500; B = 3 8090 -> 382; B = 8 of 2^26 683 (BF16x3 395) -> 185 (163). The gate rides in the
-//     kernel's arguments, so a captured graph holds all of it.
+//   B <= 9: one slice per thread wins: B = 9 of 3^17 2700 -> 370 to 470 us (314), in BF16x3
+//     1420 to 1500; B = 3 8090 -> 382; B = 8 of 2^26 683 (BF16x3 395) -> 185 (163). Where the tiles here all
+//     run at once (below 2^18 amplitudes) windows of the lowest digits are even with them (FP32: B = 8 of
+//     2^15 5.5 and 5.4, 9 of 3^9 6.0 and 6.2) and 0.2 to 0.9 us behind the split products (5.0, 5.4), which
+//     are less exact. The gate rides in the kernel's arguments, so a captured graph holds all of it.
 //   10 <= B <= 64 with a share below 0.4: k_slices_direct_lu and k_dense_mfma, which read the matrix from
 //     the state's parameter ring and so stay out of captures and of registers too small to hide the copy:
 //     B = 27 of 3^17 (0.36) 974 to 1072 -> 577 to 760, B = 12 over the 5.4e7 hybrid register 1250 -> 155,
@@ -1147,7 +1149,7 @@ static int variant_ntiles(int v) { return (v == 2 || v == 3) ? 6 : 4; }
 //     are bound by their copies, and windows that reach into the runs halve those (B = 27, window end
 //     included, 664 -> 735), so only windows above the runs change over (1003 -> 760, 457 -> 255).
 //   B = 12 and 16 where k_slices_direct_lu takes them: 372 (BF16x3 244) -> 195 us on 4^13 and 2^26.
-static bool plain_block(const qd_state* s, const FusedArgs& a, const FusedBlockDev& d, bool bf, GatePlan* p) {
+static bool plain_block(const qd_state* s, const FusedArgs& a, const FusedBlockDev& d, bool bf) {
   const int B = d.info.B;
   bool plain = B <= 9;
   if (!plain && B <= 64 && s->reg.D >= (int64_t(1) << 22)) {
@@ -1161,20 +1163,24 @@ static bool plain_block(const qd_state* s, const FusedArgs& a, const FusedBlockD
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (plain && (hipStreamIsCapturing(s->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) plain = false;
   }
-  if (!plain) return false;
-  make_plan(s->reg, d.info.window, d.info.k, nullptr, nullptr, 0, d.host64.data(), p);
-  p->cls = QD_CLASS_DENSE;   // as on the matrix cores: zeros of the block are entries like any other
+  return plain;
+}
+
+// The block as a gate of the register. It is dense as on the matrix cores: its zeros are entries like any other.
+void fused_plan(const Register& r, const FusedBlockDev& d, GatePlan* p) {
+  make_plan(r, d.info.window, d.info.k, nullptr, nullptr, 0, d.host64.data(), p);
+  p->cls = QD_CLASS_DENSE;
   p->dst.clear();
   p->ph.clear();
-  return true;
 }
 
 int launch_fused_block(qd_state* s, const qd_fused* f, int b, int mode) {
   const FusedBlockDev& d = f->dev[b];
   if (!d.geom_ok) return fail(QD_EINVAL, "fused block has no matrix-core tiling");
-  GatePlan plain;
-  if (plain_block(s, d.args, d, mode == QD_MODE_BF16X3_MFMA, &plain)) {
-    const int rc = launch_gate(s, plain);
+  if (plain_block(s, d.args, d, mode == QD_MODE_BF16X3_MFMA)) {
+    GatePlan made;
+    if (d.plain.k == 0) fused_plan(s->reg, d, &made);
+    const int rc = launch_gate(s, d.plain.k ? d.plain : made);
     if (rc != QD_ENOMEM) return rc;   // no room for the state's parameter buffer: the kernels here need none
   }
   FusedArgs a = d.args;

@@ -817,3 +817,31 @@ def test_plain_and_streaming_accesses(stream, prec, dims, gates):
             assert err <= (1e-12 if prec == Q.QD_C128 else c64_tol(len(gates), 27)), (t, c, err)
     finally:
         Q.qd_state_free(s)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("dims, t, c", [
+    ((8,) * 3, (2,), ()), ((8,) * 5, (4,), (0,)), ((9,) * 4, (3,), ()), ((7,) * 5, (4,), (2,)), ((5,) * 6, (5,), ()),
+    ((3,) * 8, (6, 7), ()), ((3,) * 9, (7, 2), (8,)), ((2,) * 14, (11, 12, 13), (3,)), ((2, 3) * 5, (9, 8), (1,)),
+    ((4,) * 7, (6,), ()), ((6,) * 4, (3,), (0,)),
+])
+def test_tiled_small_registers(stream, prec, dims, t, c):
+    """The LDS tile kernel on registers of fewer tiles than the card has compute units, d_T from 4 to 9,
+    against the oracle. One gate adds at most about c d_T u to the 2-norm."""
+    rng = C.seeded_rng(sum(dims) + 11)
+    D = O.register_size(dims)
+    psi0 = rng.standard_normal(D) + 1j * rng.standard_normal(D)
+    psi0 /= np.linalg.norm(psi0)
+    dT = int(np.prod([dims[q] for q in t]))
+    U = C.haar_unitary(dT, rng)
+    v = tuple(dims[q] - 1 for q in c)
+    s = Q.qd_state_init(dims, prec, stream)
+    try:
+        Q.qd_state_upload(s, psi0)
+        Q.qd_apply_gate(s, t, c, v, U)
+        assert Q.qd_last_kernel().startswith("k_slices_tiled")
+        out = Q.qd_state_download(s)
+    finally:
+        Q.qd_state_free(s)
+    ref = O.apply_gate(psi0, dims, t, c, v, U)
+    assert max_abs(out, ref) <= (1e-12 if prec == Q.QD_C128 else c64_tol(1, dT)), (dims, t, c, prec)

@@ -81,3 +81,28 @@ hip.host_capture(0)
 Q.qd_state_free(s)
 assert hip.host_held(DEVICE) == 0 and hip.host_held(PINNED) == 0
 """)
+
+
+def test_tiles_of_small_registers_spread_over_the_card(host_runtime):
+    """The LDS tile kernel leaves a small register enough tiles for the card (192 of 256 compute units, or
+    tiles of 256 amplitudes), whatever the radix by which tiles grow; a large one keeps tiles of about 9 KB."""
+    host_runtime("""
+def tiles(dims, prec, t):
+    s = Q.qd_state_init(dims, prec, 0)
+    hip.host_reset()
+    U = Q.qd_gate_matrix(Q.QD_GATE_F, dims[t], 0)
+    Q.qd_apply_gate(s, (t,), (), (), U)
+    Q.qd_state_free(s)
+    (name, grid, block, lds), = launches()
+    assert "k_slices_tiled" in name
+    amp = 16 if prec == Q.QD_C128 else 8
+    assert grid * lds == np.prod(dims) * amp
+    return grid, lds // amp
+for prec in (Q.QD_C128, Q.QD_C64):
+    for dims in ((8,) * 5, (4,) * 7, (7,) * 5, (9,) * 4, (5,) * 6, (2,) * 14, (3,) * 9, (2, 3) * 5):
+        n, size = tiles(dims, prec, len(dims) - 1)
+        assert n * max(dims) >= 192 or size < 256 * max(dims), (dims, prec, n, size)
+assert tiles((8,) * 5, Q.QD_C64, 4) == (64, 512)
+assert tiles((2,) * 20, Q.QD_C128, 19) == (1024, 1024) and tiles((2,) * 20, Q.QD_C64, 19) == (512, 2048)
+assert tiles((3,) * 13, Q.QD_C128, 12) == (2187, 729)
+""")
