@@ -1250,9 +1250,15 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op, const Til
   // register, 333 against 371 on 2^26; two slices for d_T = 4, where one lost up to 14 % at the highest
   // strides of 4^13: 375 to 414 against 400 to 409 us with 256 threads), with strides of 256 to 4095 128
   // threads (587 against 606). Where runs begin inside lines (3^16) each workgroup shares the lines at its
-  // ends with others, and larger ones stay ahead (271 against 289 us).
+  // ends with others, and larger ones stay ahead (271 against 289 us). On what the caches hold the smaller
+  // workgroups only add launches: they lose below 32 MB touched for a qubit (2^21 with a control, 16 MB: 6.2
+  // against 8.2 us; 2^21, 32 MB: 13.1 against 12.0) and below 64 MB for d_T = 3 (38 MB: 9.9 against 12.1) and 4
+  // (16 MB: 6.4 against 8.0; 64 MB: 21.0 against 18.6), but for d_T = 4 with strides of 256 to 4095 (2^21 with
+  // a control 7.6 against 5.7, without 11.4 against 11.9).
+  const uint64_t touched = uint64_t(a.sm.count) * DT * sizeof(R) * 2;
+  const bool large = touched >= uint64_t(DT == 2 ? 32 : 64) << 20 || (DT == 4 && min_stride < 4096);
   if (!ent.tuned && DT <= 4 && s->prec == QD_C128 && tp.direct_block == TuneParams().direct_block &&
-      tp.direct_spt == TuneParams().direct_spt && min_stride >= 256) {
+      tp.direct_spt == TuneParams().direct_spt && min_stride >= 256 && large) {
     bool lines = true;
     for (int j = 0; j < p.k; ++j) lines = lines && r.strides[p.targets[j]] % line == 0;
     for (int j = 0; j < p.m; ++j) lines = lines && r.strides[p.controls[j]] % line == 0;

@@ -106,3 +106,26 @@ assert tiles((8,) * 5, Q.QD_C64, 4) == (64, 512)
 assert tiles((2,) * 20, Q.QD_C128, 19) == (1024, 1024) and tiles((2,) * 20, Q.QD_C64, 19) == (512, 2048)
 assert tiles((3,) * 13, Q.QD_C128, 12) == (2187, 729)
 """)
+
+
+def test_direct_launch_shapes_by_touched_bytes(host_runtime):
+    """Untuned complex128 gates of d_T <= 4 take small workgroups where their passes go to HBM, and the
+    default ones where the caches hold what they touch."""
+    host_runtime("""
+def shape(dims, t, c=()):
+    s = Q.qd_state_init(dims, Q.QD_C128, 0)
+    hip.host_reset()
+    dT = int(np.prod([dims[q] for q in t]))
+    U = np.linalg.qr(np.random.default_rng(1).standard_normal((dT, dT)))[0].astype(complex)
+    Q.qd_apply_gate(s, t, c, [dims[q] - 1 for q in c], U)
+    Q.qd_state_free(s)
+    (name, grid, block, lds), = launches()
+    assert "k_slices_direct" in name
+    return block
+two = lambda n: (2,) * n
+assert shape(two(20), (0,)) == 256 and shape(two(21), (0,)) == 64          # 16 MB, 32 MB
+assert shape(two(21), (0,), (17,)) == 256 and shape(two(22), (0,), (18,)) == 64
+assert shape(two(21), (0, 1)) == 256 and shape(two(22), (0, 1)) == 64      # d_T = 4: 32 MB, 64 MB
+assert shape(two(21), (11, 12)) == 128 and shape(two(20), (11,)) == 256    # strides 512 and 256
+assert shape((3,) + two(20), (0,)) == 256 and shape((3,) + two(21), (0,)) == 64   # 50 and 100 MB
+""")
