@@ -1257,8 +1257,8 @@ static int launch_slices(qd_state* s, const GatePlan& p, const OP& op, const Til
   // a control 7.6 against 5.7, without 11.4 against 11.9).
   const uint64_t touched = uint64_t(a.sm.count) * DT * sizeof(R) * 2;
   const bool large = touched >= uint64_t(DT == 2 ? 32 : 64) << 20 || (DT == 4 && min_stride < 4096);
-  if (!ent.tuned && DT <= 4 && s->prec == QD_C128 && tp.direct_block == TuneParams().direct_block &&
-      tp.direct_spt == TuneParams().direct_spt && min_stride >= 256 && large) {
+  if (!ent.tuned && !tp.direct_block_set && !tp.direct_spt_set && DT <= 4 && s->prec == QD_C128 && min_stride >= 256 &&
+      large) {
     bool lines = true;
     for (int j = 0; j < p.k; ++j) lines = lines && r.strides[p.targets[j]] % line == 0;
     for (int j = 0; j < p.m; ++j) lines = lines && r.strides[p.controls[j]] % line == 0;

@@ -59,6 +59,8 @@ struct TuneParams {
   int batch_spt_key[QD_BATCH_KEYS] = {};
   int fused_cols = 64;      // slice columns per fused-block tile
   int run_min = 16;         // a target stride below this routes the gate to the LDS tile kernel
+  // set by the caller, also where to the default: untuned gates keep to them
+  bool direct_block_set = false, direct_spt_set = false;
 };
 TuneParams& tune();
 // key of a batched operation: composed (2+ gates) or one gate, slice size d_T, smallest target stride

@@ -819,7 +819,7 @@ int qd_tune_set(int32_t param, int32_t value) {
     case QD_TUNE_DIAG_BLOCK:
     case QD_TUNE_BATCH_BLOCK:
       if (value != 0 && (value % 64 || value > 256)) return fail(QD_EINVAL, "block must be 64, 128, 192 or 256");
-      if (param == QD_TUNE_DIRECT_BLOCK) t.direct_block = blk(value, def.direct_block);
+      if (param == QD_TUNE_DIRECT_BLOCK) t.direct_block = blk(value, def.direct_block), t.direct_block_set = value != 0;
       if (param == QD_TUNE_TILE_BLOCK) t.tile_block = blk(value, def.tile_block);
       if (param == QD_TUNE_DIAG_BLOCK) t.diag_block = blk(value, def.diag_block);
       if (param == QD_TUNE_BATCH_BLOCK) t.batch_block = blk(value, def.batch_block);
@@ -827,6 +827,7 @@ int qd_tune_set(int32_t param, int32_t value) {
     case QD_TUNE_DIRECT_SPT:
       if (value != 0 && value != 1 && value != 2 && value != 4) return fail(QD_EINVAL, "slices per thread must be 1, 2 or 4");
       t.direct_spt = blk(value, def.direct_spt);
+      t.direct_spt_set = value != 0;
       return QD_OK;
     case QD_TUNE_BATCH_SPT:
       if (value != 0 && value != 1 && value != 2 && value != 4 && value != 8)

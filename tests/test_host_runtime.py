@@ -129,3 +129,29 @@ assert shape(two(21), (0, 1)) == 256 and shape(two(22), (0, 1)) == 64      # d_T
 assert shape(two(21), (11, 12)) == 128 and shape(two(20), (11,)) == 256    # strides 512 and 256
 assert shape((3,) + two(20), (0,)) == 256 and shape((3,) + two(21), (0,)) == 64   # 50 and 100 MB
 """)
+
+
+def test_explicit_direct_settings_hold(host_runtime):
+    """A workgroup size or a number of slices per thread that the caller has set is what gates run with, also
+    where it is the default's; 0 gives the shapes of untuned gates back."""
+    host_runtime("""
+s = Q.qd_state_init((2,) * 24, Q.QD_C128, 0)
+U = Q.qd_gate_matrix(Q.QD_GATE_F, 2, 0)
+def shape():
+    hip.host_reset()
+    Q.qd_apply_gate(s, (0,), (), (), U)
+    (name, grid, block, lds), = launches()
+    return block, (1 << 23) // (grid * block)
+assert shape() == (64, 1)
+for param, value, want in ((Q.QD_TUNE_DIRECT_BLOCK, 256, (256, 2)), (Q.QD_TUNE_DIRECT_SPT, 2, (256, 2)),
+                           (Q.QD_TUNE_DIRECT_BLOCK, 128, (128, 2)), (Q.QD_TUNE_DIRECT_SPT, 4, (256, 4))):
+    Q.qd_tune_set(param, value)
+    assert shape() == want, (param, value, shape())
+    Q.qd_tune_set(param, 0)
+    assert shape() == (64, 1)
+Q.qd_tune_set(Q.QD_TUNE_DIRECT_BLOCK, 256)
+Q.qd_tune_set(Q.QD_TUNE_DIRECT_SPT, 0)
+assert shape() == (256, 2)
+Q.qd_tune_set(Q.QD_TUNE_DIRECT_BLOCK, 0)
+Q.qd_state_free(s)
+""")
