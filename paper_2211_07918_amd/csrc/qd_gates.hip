@@ -1014,14 +1014,16 @@ bool tile_geometry(const Register& r, const GatePlan& p, int prec, TileGeom* g) 
     if (nsc > kMaxTileCtl) return false;
     for (int i = 0; i < pq; ++i)
       if (is_t[i]) dH *= r.dims[i];
-    // Growth stops at 9 KB: more, smaller tiles keep the memory system busier than few large ones
-    // (complex128: 648 against 1296 amplitudes 565 and 615 us on the hybrid register of 1.1e8, 1024
-    // against 2048 178 and 197 us on 2^25), while tiles below that size leave the workgroups short of
-    // loads (243 against 729 amplitudes 384 and 243 us on 3^16; complex64: 729 against 2187 221 and 132 us).
+    // A tuned tile or one that the caller has set is filled. Otherwise growth stops at 9 KB: more, smaller
+    // tiles keep the memory system busier than few large ones (complex128: 648 against 1296 amplitudes 565
+    // and 615 us on the hybrid register of 1.1e8, 1024 against 2048 178 and 197 us on 2^25), while tiles
+    // below that size leave the workgroups short of loads (243 against 729 amplitudes 384 and 243 us on
+    // 3^16; complex64: 729 against 2187 221 and 132 us).
     // A register of fewer than 192 tiles of that size (of 256 CUs) takes smaller ones, down to one amplitude
     // a thread: complex64, radix 8 on 2^15 amplitudes 7.2 -> 5.2 us with 64 tiles instead of 8, 9 x 9 gates on
     // 3^9 6.4 -> 6.0; tiles of 64 amplitudes are slower again (5.7 and 6.1).
-    const uint64_t enough = 9216 / amp_bytes(prec);
+    const bool fill = e.tuned || tp.tile_elems_set;
+    const uint64_t enough = fill ? emax : 9216 / amp_bytes(prec);
     while (pq > 0 && BL * dH < enough) {
       const int q = pq - 1;
       const bool drop = compact && is_c[q];
@@ -1029,7 +1031,7 @@ bool tile_geometry(const Register& r, const GatePlan& p, int prec, TileGeom* g) 
       const uint64_t nBL = drop ? BL : BL * r.dims[q];
       const uint64_t ndH = is_t[q] ? dH / r.dims[q] : dH;
       if (nBL * ndH > emax) break;
-      if (BL * dH >= 256 && nBL * ndH * 192 > uint64_t(r.D)) break;
+      if (!fill && BL * dH >= 256 && nBL * ndH * 192 > uint64_t(r.D)) break;
       pq = q;
       BL = nBL;
       dH = ndH;

@@ -47,7 +47,8 @@ struct TuneParams {
   int direct_block = 256;   // threads per workgroup, slice-per-thread kernels
   int direct_spt = 2;       // slices per thread
   int tile_block = 256;     // threads per workgroup, LDS-tiled kernels
-  int tile_elems = 2048;    // amplitudes per LDS tile (complex128; doubled for complex64)
+  int tile_elems = 2048;    // most amplitudes of an LDS tile (complex128; doubled for complex64); one that is set
+                            // is filled, untuned tiles stop at 9 KB
   int diag_block = 256;
   int batch_block = 256;
   int batch_spt = 4;
@@ -60,7 +61,7 @@ struct TuneParams {
   int fused_cols = 64;      // slice columns per fused-block tile
   int run_min = 16;         // a target stride below this routes the gate to the LDS tile kernel
   // set by the caller, also where to the default: untuned gates keep to them
-  bool direct_block_set = false, direct_spt_set = false;
+  bool direct_block_set = false, direct_spt_set = false, tile_elems_set = false;
 };
 TuneParams& tune();
 // key of a batched operation: composed (2+ gates) or one gate, slice size d_T, smallest target stride

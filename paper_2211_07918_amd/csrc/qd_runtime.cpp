@@ -837,6 +837,7 @@ int qd_tune_set(int32_t param, int32_t value) {
     case QD_TUNE_TILE_ELEMS:
       if (value != 0 && (value < 256 || value > 4096 || (value & (value - 1)))) return fail(QD_EINVAL, "tile must be a power of two in 256..4096");
       t.tile_elems = blk(value, def.tile_elems);
+      t.tile_elems_set = value != 0;
       return QD_OK;
     case QD_TUNE_FUSED_COLS:
       if (value != 0 && value != 32 && value != 64 && value != 128) return fail(QD_EINVAL, "fused columns must be 32, 64 or 128");

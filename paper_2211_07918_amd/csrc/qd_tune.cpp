@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "qd_internal.h"
@@ -125,13 +126,18 @@ int qd_autotune(qd_state* s, const char* path) {
     for (int te : {512, 1024, 2048, 4096})
       for (int blk : {128, 256}) cands.push_back(TuneEntry{1, 1, blk, 1, te});
     float best = 1e30f;
+    std::vector<std::pair<int, uint64_t>> seen;   // workgroup and tile of the tiled candidates timed
     for (const TuneEntry& c : cands) {
       g_table[p][b] = c;
       g_table_valid = true;
-      // a tiled candidate that cannot form a tile runs the direct kernel: skip it
+      // a tiled candidate that cannot form a tile runs the direct kernel, one that forms an earlier one's
+      // tile is the same launch: skip both
       if (c.tiled) {
         TileGeom g;
         if (!tile_geometry(s->reg, plan, s->prec, &g)) continue;
+        const std::pair<int, uint64_t> tile(c.block, g.BL * g.dH);
+        if (std::find(seen.begin(), seen.end(), tile) != seen.end()) continue;
+        seen.push_back(tile);
       }
       float ms = 0.f;
       rc = time_gate(s, plan, &ms);

@@ -155,3 +155,47 @@ assert shape() == (256, 2)
 Q.qd_tune_set(Q.QD_TUNE_DIRECT_BLOCK, 0)
 Q.qd_state_free(s)
 """)
+
+
+def test_tile_elems_choose_the_tile(host_runtime, tmp_path):
+    """QD_TUNE_TILE_ELEMS and tuned entries say how large a tile grows; untuned tiles stop at 9 KB whatever
+    the budget. The autotuner times no launch twice under two names."""
+    host_runtime(f"""
+path = {str(tmp_path / "tune.json")!r}
+def tile(dims, prec):
+    s = Q.qd_state_init(dims, prec, 0)
+    hip.host_reset()
+    Q.qd_apply_gate(s, (len(dims) - 1,), (), (), Q.qd_gate_matrix(Q.QD_GATE_F, dims[-1], 0))
+    (name, grid, block, lds), = launches()
+    assert "k_slices_tiled" in name
+    Q.qd_state_free(s)
+    return lds // (16 if prec == Q.QD_C128 else 8)
+""" + """
+for prec, untuned in ((Q.QD_C128, 1024), (Q.QD_C64, 2048)):
+    dims, full = (2,) * 22, 2048 if prec == Q.QD_C128 else 4096       # 256 threads of 8 or 16 amplitudes
+    assert tile(dims, prec) == untuned
+    for elems in (256, 512, 1024, 2048, 4096):
+        Q.qd_tune_set(Q.QD_TUNE_TILE_ELEMS, elems)
+        assert tile(dims, prec) == min(elems * full // 2048, full), (prec, elems)
+    assert tile((3,) * 13, prec) == (729 if prec == Q.QD_C128 else 2187)
+    Q.qd_tune_set(Q.QD_TUNE_TILE_ELEMS, 0)
+    assert tile(dims, prec) == untuned
+    for elems in (512, 2048):
+        with open(path, "w") as f:
+            f.write("[\\n{\\"prec\\": %d, \\"bucket\\": 0, \\"tiled\\": 1, \\"block\\": 256, \\"spt\\": 1, \\"tile_elems\\": %d}\\n]\\n"
+                    % (prec, elems))
+        Q.qd_tune_load(path)
+        assert tile(dims, prec) == min(elems * full // 2048, full), (prec, elems)
+    Q.qd_tune_set(Q.QD_TUNE_TILE_ELEMS, 0)                             # discards the table
+    s = Q.qd_state_init(dims, prec, 0)
+    hip.host_reset()
+    Q.qd_autotune(s, None)
+    Q.qd_state_free(s)
+    runs = [[]]                                                        # the tiled candidates of each stride class
+    for name, *shape in launches():
+        if "k_slices_tiled" not in name: runs.append([])
+        else: runs[-1].append(tuple(shape))
+    runs = [r for r in runs if r]
+    assert runs and all(len(r) == 11 * len(set(r)) for r in runs), [(len(r), len(set(r))) for r in runs]    # 11 launches time one
+    Q.qd_tune_set(Q.QD_TUNE_RUN_MIN, 0)
+""")
