@@ -319,3 +319,29 @@ def expected_passes(ops, dims):
         composed += alone(ops[i]) if j - i == 1 else 1
         i = j
     return composed, sum(alone(o) for o in ops)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+def test_large_superoperators_between_small_ones(stream, prec):
+    """qd_density_apply_ops applies its list so far whenever it holds a superoperator of 1 MB (d_T = 16 here):
+    the same matrix as one call for each operation. Each adds at most about 4 d_T^2 u."""
+    dims = (2, 16, 3)
+    rng = C.seeded_rng(61)
+    kraus = lambda q, p: Dm.depolarizing(dims[q], p)
+    mixed = [np.sqrt(0.3) * C.haar_unitary(16, rng), np.sqrt(0.7) * C.haar_unitary(16, rng)]
+    ops = [("chan", (0,), kraus(0, 0.1)), ("chan", (2,), kraus(2, 0.2)), ("chan", (1,), mixed), ("chan", (2,), kraus(2, 0.1)),
+           ("gate", C.Gate("U", (1,), (0,), (1,), U=C.haar_unitary(16, rng))), ("chan", (0,), kraus(0, 0.2)),
+           ("chan", (1,), mixed), ("chan", (2,), kraus(2, 0.05))]
+    want = Dm.from_state(O.basis_state(dims))
+    for o in ops:
+        if o[0] == "gate":
+            want = Dm.apply_unitary(want, dims, o[1].targets, o[1].controls, o[1].cvals, O.gate_unitary(o[1], dims))
+        else:
+            want = Dm.apply_channel(want, dims, o[1], o[2])
+    rho = Q.qd_density_init(dims, prec, stream)
+    try:
+        Q.qd_density_apply_ops(rho, ops)
+        got = download_rho(rho, dims)
+    finally:
+        Q.qd_state_free(rho)
+    assert np.max(np.abs(got - want)) <= (1e-12 if prec == Q.QD_C128 else 4.0 * len(ops) * 256 * 2.0 ** -24)

@@ -199,3 +199,29 @@ for prec, untuned in ((Q.QD_C128, 1024), (Q.QD_C64, 2048)):
     assert runs and all(len(r) == 11 * len(set(r)) for r in runs), [(len(r), len(set(r))) for r in runs]    # 11 launches time one
     Q.qd_tune_set(Q.QD_TUNE_RUN_MIN, 0)
 """)
+
+
+def test_density_operations_hold_a_bounded_list(host_runtime):
+    """A superoperator on d_T = 32 takes 16.8 MB: sixty in one call need the memory of a few. Small
+    operations still share passes."""
+    host_runtime("""
+import resource
+rho = Q.qd_density_init((32, 2), Q.QD_C64, 0)
+K = np.eye(32, dtype=complex)
+chan = ("chan", (0,), [K])
+Q.qd_density_apply_ops(rho, [chan, chan])
+before = resource.getrusage(resource.RUSAGE_SELF).ru_maxrss
+hip.host_reset()
+Q.qd_density_apply_ops(rho, [chan] * 60)
+grown = (resource.getrusage(resource.RUSAGE_SELF).ru_maxrss - before) * 1024
+assert grown < 200e6, grown
+assert len(launches()) == 60
+Q.qd_state_free(rho)
+rho = Q.qd_density_init((3, 2, 3, 2), Q.QD_C128, 0)
+dep = lambda q, d: ("chan", (q,), Q.qd_channel_kraus(Q.QD_CHANNEL_DEPOLARIZING, d, 0.1))
+hip.host_reset()
+Q.qd_density_apply_ops(rho, [dep(q, (3, 2, 3, 2)[q]) for q in (0, 1, 2, 3, 0, 2)])
+(name, *_), = launches()
+assert "k_window" in name
+Q.qd_state_free(rho)
+""")
