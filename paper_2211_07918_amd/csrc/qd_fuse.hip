@@ -89,7 +89,7 @@ int plan_fusion(const Register& r, const qd_gate* gates, int32_t g, int32_t max_
 // Real embedding of a complex B x B block U with interleaved rows/columns: row 2y'+c', column
 // 2y+c carries the 2x2 real block [[Re u, -Im u], [Im u, Re u]] of u = U[y', y]. Padded with zeros
 // to Kp x Kp, row-major FP32, plus the BF16 split hi = bf16(a), lo = bf16(a - hi).
-// One launch for all blocks of a circuit, blockIdx.y the block.
+// One launch for all blocks of a group, blockIdx.y the block.
 struct EmbedJob {
   const double* U;
   float* a32;
@@ -126,6 +126,141 @@ size_t fused_stage(std::vector<char>* image, const void* src, size_t bytes) {
 }
 
 static int pad_k(int B) { return fused_kpad(B); }
+
+// Blocks built together: their image takes 8 MB of pinned memory, which one block after the other used to
+// share, and their tables' share of it stays small.
+constexpr size_t kGroupBytes = size_t(8) << 20;
+constexpr size_t kGroupBlocks = 256;
+
+struct FuseStaging {
+  ParamRing ring;           // one parameter ring for all blocks
+  char* pinned = nullptr;
+  size_t cap = 0;
+};
+
+// Builds blocks [b0, b1). Everything they need lies in one device allocation: an image that is uploaded in
+// one copy (the blocks, each the identity; the tables of their tilings; the jobs of k_embed), the parameter
+// ring of the gates that build them, and the real embeddings. The blocks are built one after the other on
+// the stream, come back in one copy, and the call waits once. With an allocation, a copy and a wait for each
+// table and block, 60 gates on 15 qudits in 11 blocks took 1.82 ms of host time; now 0.32.
+static int fuse_group(qd_fused* f, const qd_gate* gates, size_t b0, size_t b1, FuseStaging* st) {
+  const Register& r = f->reg;
+  const size_t nb = b1 - b0;
+  FusedBlockDev* dev = f->dev.data() + b0;
+  std::vector<char> image;
+  std::vector<size_t> u_at(nb), a_at(nb);
+  for (size_t b = 0; b < nb; ++b) {
+    FusedBlockDev& d = dev[b];
+    d.Kp = pad_k(d.info.B);
+    // identity: amplitude (row, col) = delta(row, col) at flat index row * B + col
+    const int B = d.info.B;
+    d.host64.assign(2 * size_t(B) * B, 0.0);
+    for (int y = 0; y < B; ++y) d.host64[2 * (size_t(y) * B + y)] = 1.0;
+    u_at[b] = fused_stage(&image, d.host64.data(), d.host64.size() * sizeof(double));
+  }
+  const size_t u_bytes = image.size();
+  if (r.D <= int64_t(0xFFFFFFFFll))
+    for (size_t b = 0; b < nb; ++b) {
+      int rc = fused_geometry(r, &dev[b], &image);
+      if (rc) return rc;
+    }
+  std::vector<EmbedJob> jobs(nb);
+  const size_t jobs_at = fused_stage(&image, jobs.data(), nb * sizeof(EmbedJob));
+  const size_t ring_at = (image.size() + 255) & ~size_t(255), up = ring_at + st->ring.first;
+  size_t total = up;
+  int kmax = 0;
+  for (size_t b = 0; b < nb; ++b) {
+    a_at[b] = total;
+    total += size_t(dev[b].Kp) * dev[b].Kp * 8;   // FP32, two BF16 (Kp a multiple of 64)
+    kmax = std::max(kmax, dev[b].Kp);
+  }
+  if (up > st->cap) {   // (the stream has been waited for)
+    if (st->pinned) (void)hipHostFree(st->pinned);
+    st->pinned = nullptr;
+    st->cap = 0;
+    QD_HIP(hipHostMalloc((void**)&st->pinned, up, hipHostMallocDefault));
+    st->cap = up;
+  }
+  char* arena = nullptr;
+  QD_HIP(dev_malloc((void**)&arena, total));
+  f->arenas.push_back(arena);
+  char* pinned = st->pinned;
+  if (st->ring.lent || !st->ring.host) {
+    st->ring.host = pinned + ring_at;
+    st->ring.dev = arena + ring_at;
+    st->ring.cap = st->ring.first;
+    st->ring.head = 0;
+    st->ring.lent = true;
+  }
+  for (size_t b = 0; b < nb; ++b) {
+    FusedBlockDev& d = dev[b];
+    const size_t kk = size_t(d.Kp) * d.Kp;
+    d.u64 = reinterpret_cast<double*>(arena + u_at[b]);
+    d.a32 = reinterpret_cast<float*>(arena + a_at[b]);
+    d.ahi = reinterpret_cast<__hip_bfloat16*>(d.a32 + kk);
+    d.alo = d.ahi + kk;
+    if (d.geom_ok) fused_bind(&d, arena);
+    jobs[b] = EmbedJob{d.u64, d.a32, d.ahi, d.alo, d.info.B, d.Kp};
+  }
+  std::memcpy(pinned, image.data(), image.size());
+  std::memcpy(pinned + jobs_at, jobs.data(), nb * sizeof(EmbedJob));
+  QD_HIP(hipMemcpyAsync(arena, pinned, image.size(), hipMemcpyHostToDevice, f->stream));
+  for (size_t b = 0; b < nb; ++b) {
+    FusedBlockDev& d = dev[b];
+    const int B = d.info.B;
+    // The block is built by applying its gates, embedded in the window register, to the
+    // identity: a register with the window's dims plus the column index as lowest digits, so
+    // M <- E_g M for every column at once (FP64, the plain gate kernels). The column index counts as
+    // two digits, the lower about one line long, so that a few columns make a tile and the block's
+    // gates run in one pass.
+    int32_t wdims[QD_MAX_QUDITS + 2];
+    int pos[QD_MAX_QUDITS];
+    for (int j = 0; j < d.info.k; ++j) {
+      wdims[j] = r.dims[d.info.window[j]];
+      pos[d.info.window[j]] = j;
+    }
+    int low = 1;
+    for (int c : {8, 9, 10, 11, 12, 13, 14, 15, 16, 7, 6, 5, 4, 3, 2})
+      if (B % c == 0 && B > c && low == 1) low = c;
+    int wn = d.info.k;
+    if (low > 1) wdims[wn++] = B / low;
+    wdims[wn++] = low > 1 ? low : B;
+    qd_state tmp;
+    int rc = make_register(wdims, wn, &tmp.reg);
+    if (rc) return rc;
+    tmp.prec = QD_C128;
+    tmp.data = d.u64;
+    tmp.owned = false;
+    tmp.stream = f->stream;
+    tmp.ring = st->ring;
+    std::vector<int32_t> at;   // the members' targets and controls as window positions
+    for (int i : d.info.members)
+      for (int j = 0; j < gates[i].k + gates[i].m; ++j)
+        at.push_back(pos[j < gates[i].k ? gates[i].targets[j] : gates[i].controls[j - gates[i].k]]);
+    std::vector<GateRef> list;
+    const int32_t* q = at.data();
+    for (int i : d.info.members) {
+      const qd_gate& G = gates[i];
+      list.push_back(GateRef{q, G.k, q + G.k, G.control_values, G.m, G.U});
+      q += G.k + G.m;
+    }
+    rc = apply_gate_list(&tmp, list);
+    st->ring = tmp.ring;
+    if (rc) return rc;
+  }
+  hipLaunchKernelGGL(k_embed, dim3(std::min(64, (kmax * kmax + 255) / 256), unsigned(nb)), dim3(256), 0, f->stream,
+                     reinterpret_cast<const EmbedJob*>(arena + jobs_at));
+  QD_HIP(hipGetLastError());
+  // host copies of the FP64 blocks for the FP64 apply path (the image has been read by then)
+  QD_HIP(hipMemcpyAsync(pinned, arena, u_bytes, hipMemcpyDeviceToHost, f->stream));
+  QD_HIP(hipStreamSynchronize(f->stream));
+  for (size_t b = 0; b < nb; ++b) {
+    FusedBlockDev& d = dev[b];
+    std::memcpy(d.host64.data(), pinned + u_at[b], d.host64.size() * sizeof(double));
+    if (d.geom_ok && d.info.B <= 9) fused_plan(r, d, &d.plain);
+  }
+  return QD_OK;
+}
 
 }  // namespace qd
 
@@ -188,134 +323,26 @@ int qd_fuse(const int32_t* dims, int32_t n, const qd_gate* gates, int32_t g, int
   f->reg = r;
   f->stream = (hipStream_t)hip_stream;
   f->dev.resize(blocks.size());
-  const size_t nb = blocks.size();
-  char* pinned = nullptr;
-  ParamRing ring;
-  ring.first = size_t(256) << 10;
-  auto cleanup = [&](int code) {
-    (void)hipStreamSynchronize(f->stream);
-    ring_free(&ring);
-    if (pinned) (void)hipHostFree(pinned);
+  for (size_t b = 0; b < blocks.size(); ++b) f->dev[b].info = blocks[b];
+  FuseStaging st;
+  st.ring.first = size_t(256) << 10;
+  for (size_t b = 0; b < blocks.size() && !rc;) {
+    size_t e = b, bytes = 0;
+    while (e < blocks.size() && e - b < kGroupBlocks) {
+      bytes += 16 * size_t(blocks[e].B) * blocks[e].B;
+      if (e > b && bytes > kGroupBytes) break;
+      ++e;
+    }
+    rc = fuse_group(f, gates, b, e, &st);
+    b = e;
+  }
+  (void)hipStreamSynchronize(f->stream);
+  ring_free(&st.ring);
+  if (st.pinned) (void)hipHostFree(st.pinned);
+  if (rc) {
     qd_fused_free(f);
-    return code;
-  };
-  // Everything a block needs lies in one device allocation: an image that is uploaded in one copy (the
-  // blocks, each the identity; the tables of their tilings; the jobs of k_embed), the parameter ring of
-  // the gates that build them, and the real embeddings. The blocks are built one after the other on the
-  // stream, come back in one copy, and the call waits once. With an allocation, a copy and a wait for each
-  // table and block, 60 gates on 15 qudits in 11 blocks took 1.82 ms of host time; now 0.32.
-  std::vector<char> image;
-  std::vector<size_t> u_at(nb), a_at(nb);
-  for (size_t b = 0; b < nb; ++b) {
-    FusedBlockDev& d = f->dev[b];
-    d.info = blocks[b];
-    d.Kp = pad_k(d.info.B);
-    // identity: amplitude (row, col) = delta(row, col) at flat index row * B + col
-    const int B = d.info.B;
-    d.host64.assign(2 * size_t(B) * B, 0.0);
-    for (int y = 0; y < B; ++y) d.host64[2 * (size_t(y) * B + y)] = 1.0;
-    u_at[b] = fused_stage(&image, d.host64.data(), d.host64.size() * sizeof(double));
+    return rc;
   }
-  const size_t u_bytes = image.size();
-  if (r.D <= int64_t(0xFFFFFFFFll))
-    for (size_t b = 0; b < nb; ++b) {
-      rc = fused_geometry(r, &f->dev[b], &image);
-      if (rc) return cleanup(rc);
-    }
-  std::vector<EmbedJob> jobs(nb);
-  const size_t jobs_at = fused_stage(&image, jobs.data(), nb * sizeof(EmbedJob));
-  const size_t ring_at = (image.size() + 255) & ~size_t(255), up = ring_at + ring.first;
-  size_t total = up;
-  int kmax = 0;
-  for (size_t b = 0; b < nb; ++b) {
-    a_at[b] = total;
-    total += size_t(f->dev[b].Kp) * f->dev[b].Kp * 8;   // FP32, two BF16 (Kp a multiple of 64)
-    kmax = std::max(kmax, f->dev[b].Kp);
-  }
-  if (nb) {
-    hipError_t e = dev_malloc((void**)&f->arena, total);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&pinned, up, hipHostMallocDefault);
-    if (e != hipSuccess) return cleanup(hip_fail(e, "fused block allocation"));
-    ring.host = pinned + ring_at;
-    ring.dev = f->arena + ring_at;
-    ring.cap = ring.first;
-    ring.lent = true;
-    for (size_t b = 0; b < nb; ++b) {
-      FusedBlockDev& d = f->dev[b];
-      const size_t kk = size_t(d.Kp) * d.Kp;
-      d.u64 = reinterpret_cast<double*>(f->arena + u_at[b]);
-      d.a32 = reinterpret_cast<float*>(f->arena + a_at[b]);
-      d.ahi = reinterpret_cast<__hip_bfloat16*>(d.a32 + kk);
-      d.alo = d.ahi + kk;
-      if (d.geom_ok) fused_bind(&d, f->arena);
-      jobs[b] = EmbedJob{d.u64, d.a32, d.ahi, d.alo, d.info.B, d.Kp};
-    }
-    std::memcpy(pinned, image.data(), image.size());
-    std::memcpy(pinned + jobs_at, jobs.data(), nb * sizeof(EmbedJob));
-    e = hipMemcpyAsync(f->arena, pinned, image.size(), hipMemcpyHostToDevice, f->stream);
-    if (e != hipSuccess) return cleanup(hip_fail(e, "fused block init"));
-  }
-  for (size_t b = 0; b < nb; ++b) {
-    FusedBlockDev& d = f->dev[b];
-    const int B = d.info.B;
-    // The block is built by applying its gates, embedded in the window register, to the
-    // identity: a register with the window's dims plus the column index as lowest digits, so
-    // M <- E_g M for every column at once (FP64, the plain gate kernels). The column index counts as
-    // two digits, the lower about one line long, so that a few columns make a tile and the block's
-    // gates run in one pass.
-    int32_t wdims[QD_MAX_QUDITS + 2];
-    int pos[QD_MAX_QUDITS];
-    for (int j = 0; j < d.info.k; ++j) {
-      wdims[j] = r.dims[d.info.window[j]];
-      pos[d.info.window[j]] = j;
-    }
-    int low = 1;
-    for (int c : {8, 9, 10, 11, 12, 13, 14, 15, 16, 7, 6, 5, 4, 3, 2})
-      if (B % c == 0 && B > c && low == 1) low = c;
-    int wn = d.info.k;
-    if (low > 1) wdims[wn++] = B / low;
-    wdims[wn++] = low > 1 ? low : B;
-    qd_state tmp;
-    rc = make_register(wdims, wn, &tmp.reg);
-    if (rc) return cleanup(rc);
-    tmp.prec = QD_C128;
-    tmp.data = d.u64;
-    tmp.owned = false;
-    tmp.stream = f->stream;
-    tmp.ring = ring;
-    std::vector<int32_t> at;   // the members' targets and controls as window positions
-    for (int i : d.info.members)
-      for (int j = 0; j < gates[i].k + gates[i].m; ++j)
-        at.push_back(pos[j < gates[i].k ? gates[i].targets[j] : gates[i].controls[j - gates[i].k]]);
-    std::vector<GateRef> list;
-    const int32_t* q = at.data();
-    for (int i : d.info.members) {
-      const qd_gate& G = gates[i];
-      list.push_back(GateRef{q, G.k, q + G.k, G.control_values, G.m, G.U});
-      q += G.k + G.m;
-    }
-    rc = apply_gate_list(&tmp, list);
-    ring = tmp.ring;   // one parameter ring for all blocks
-    if (rc) return cleanup(rc);
-  }
-  if (nb) {
-    for (size_t b = 0; b < nb; b += 65535)   // the largest grid in y
-      hipLaunchKernelGGL(k_embed, dim3(std::min(64, (kmax * kmax + 255) / 256), unsigned(std::min<size_t>(nb - b, 65535))),
-                         dim3(256), 0, f->stream, reinterpret_cast<const EmbedJob*>(f->arena + jobs_at) + b);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return cleanup(hip_fail(e, "fused block embedding"));
-    // host copies of the FP64 blocks for the FP64 apply path (the image has been read by then)
-    e = hipMemcpyAsync(pinned, f->arena, u_bytes, hipMemcpyDeviceToHost, f->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(f->stream);
-    if (e != hipSuccess) return cleanup(hip_fail(e, "fused block build"));
-    for (size_t b = 0; b < nb; ++b) {
-      FusedBlockDev& d = f->dev[b];
-      std::memcpy(d.host64.data(), pinned + u_at[b], d.host64.size() * sizeof(double));
-      if (d.geom_ok && d.info.B <= 9) fused_plan(r, d, &d.plain);
-    }
-  }
-  ring_free(&ring);
-  if (pinned) (void)hipHostFree(pinned);
   *out = f;
   return QD_OK;
 }
@@ -388,7 +415,7 @@ int qd_apply_fused(qd_state* s, const qd_fused* f, int32_t mode_flags) {
 void qd_fused_free(qd_fused* f) {
   if (!f) return;
   (void)hipStreamSynchronize(f->stream);
-  if (f->arena) (void)hipFree(f->arena);
+  for (char* a : f->arenas) (void)hipFree(a);
   delete f;
 }
 

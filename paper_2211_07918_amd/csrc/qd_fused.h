@@ -90,5 +90,5 @@ struct qd_fused {
   qd::Register reg;
   hipStream_t stream = nullptr;
   std::vector<qd::FusedBlockDev> dev;
-  char* arena = nullptr;            // one device allocation: everything the blocks point to
+  std::vector<char*> arenas;        // device allocations: everything the blocks point to, one for each group
 };

@@ -23,6 +23,7 @@ int fail(int code, const std::string& msg) {
 
 int hip_fail(hipError_t e, const char* what) {
   std::string m = std::string(what) + ": " + hipGetErrorString(e);
+  (void)hipGetLastError();   // reported here, not by the next launch's check
   return fail(e == hipErrorOutOfMemory ? QD_ENOMEM : QD_EDEVICE, m);
 }
 
@@ -496,7 +497,6 @@ int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out
       if (e == hipSuccess) e = dev_malloc((void**)&r->dev, r->cap);
     }
     if (e != hipSuccess) {   // none of it is kept: the next call tries both again
-      (void)hipGetLastError();
       ring_free(r);
       return hip_fail(e, "parameter buffer");
     }

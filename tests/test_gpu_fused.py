@@ -466,3 +466,33 @@ def test_small_blocks_under_capture():
             Q.qd_state_free(h)
         for f in fs:
             Q.qd_fused_free(f)
+
+
+def test_blocks_of_several_groups(stream):
+    """Blocks are built in groups of at most 8 MB: a circuit of 60 blocks of 128 (16 MB) leaves the state
+    that its gates leave one by one, in FP64 and in FP32 (each gate adds about d_T u to the 2-norm)."""
+    dims = (2,) * 14
+    rng = C.seeded_rng(101)
+    gates = []
+    for i in range(60):
+        w = [int(q) for q in rng.permutation(14)[:7]]
+        gates += [C.Gate("U", tuple(w[a:a + 2]), U=C.haar_unitary(4, rng)) for a in (0, 2, 4, 5)]
+    f = fuse(C.Circuit(dims, gates), 128, stream)
+    psi0 = rng.standard_normal(2 ** 14) + 1j * rng.standard_normal(2 ** 14)
+    psi0 /= np.linalg.norm(psi0)
+    ref = psi0
+    for g in gates:
+        ref = O.apply_gate(ref, dims, g.targets, (), (), g.U)
+    try:
+        assert sum(16 * Q.qd_fused_block_info(f, b)["B"] ** 2 for b in range(Q.qd_fused_count(f))) > 8 << 20
+        for prec, mode, tol in ((Q.QD_C128, Q.QD_MODE_FP64_PLAIN, 1e-12),
+                                (Q.QD_C64, Q.QD_MODE_FP32_MFMA, 4 * 60 * 128 * 2.0 ** -24)):
+            s = Q.qd_state_init(dims, prec, stream)
+            try:
+                Q.qd_state_upload(s, psi0)
+                Q.qd_apply_fused(s, f, mode)
+                assert np.linalg.norm(Q.qd_state_download(s) - ref) <= tol
+            finally:
+                Q.qd_state_free(s)
+    finally:
+        Q.qd_fused_free(f)

@@ -225,3 +225,35 @@ Q.qd_density_apply_ops(rho, [dep(q, (3, 2, 3, 2)[q]) for q in (0, 1, 2, 3, 0, 2)
 assert "k_window" in name
 Q.qd_state_free(rho)
 """)
+
+
+def test_fusing_stages_through_a_bounded_pinned_buffer(host_runtime):
+    """Two thousand blocks of 81 x 81 (0.2 GB) pass through some 9 MB of pinned memory, and a call that finds
+    no room for a later group leaves nothing behind; a small circuit still waits for the GPU once."""
+    host_runtime("""
+dims = (3,) * 12
+U = np.linalg.qr(np.random.default_rng(1).standard_normal((81, 81)))[0].astype(complex)
+def gate(t): return type("G", (), dict(kind="U", targets=t, controls=(), cvals=(), a=0, U=U))
+ga = Q.GateArray([gate((0, 1, 2, 3 + i % 2)) for i in range(2000)], lambda i: dims)
+f = Q.qd_fuse(dims, ga, 81, 0)
+assert Q.qd_fused_count(f) == 2000
+assert hip.host_peak(PINNED) < 10 << 20, hip.host_peak(PINNED)
+assert hip.host_held(PINNED) == 0
+whole = hip.host_held(DEVICE)
+Q.qd_fused_free(f)
+assert hip.host_held(DEVICE) == 0
+hip.host_limit(DEVICE, whole // 2)
+try:
+    Q.qd_fuse(dims, ga, 81, 0)
+    raise AssertionError("half of the memory was enough")
+except Q.QDError as e:
+    assert e.code == Q.QD_ENOMEM
+hip.host_limit(DEVICE, -1)
+assert hip.host_held(DEVICE) == 0 and hip.host_held(PINNED) == 0
+hip.host_reset()
+V = Q.qd_gate_matrix(Q.QD_GATE_F, 3, 0)
+small = [type("G", (), dict(kind="U", targets=(q,), controls=(), cvals=(), a=0, U=V)) for q in range(12)]
+f = Q.qd_fuse(dims, small, 9, 0)
+assert Q.qd_fused_count(f) == 6 and hip.host_waits() <= 2
+Q.qd_fused_free(f)
+""")
