@@ -102,6 +102,10 @@ const char* qd_last_kernel(void);
  * Host counter, no synchronisation. QD_EINVAL for a null argument. */
 int qd_state_gate_launches(const qd_state* s, int64_t* out);
 
+/* Trips over the state that those passes took: kernel launches, one for the passes that share a window
+ * of the register. Host counter, no synchronisation. QD_EINVAL for a null argument. */
+int qd_state_gate_trips(const qd_state* s, int64_t* out);
+
 /* Register table (Sec. 2.2: the state has prod dims[i] entries). Host only, no device work.
  * Writes D to *D_out and the n big-endian strides to strides_out[n] (caller-allocated).
  * QD_EINVAL for n outside 1..64 or null pointers, QD_EDIM for a radix outside 2..256,

@@ -712,13 +712,19 @@ int qd_apply_gate_ex(qd_state* s, const int32_t* targets, int32_t k, const int32
   GatePlan p;
   plan_gate(s->reg, s->prec, targets, k, controls, control_values, m, U, &p);
   rc = launch_gate(s, p);
-  if (rc == QD_OK && last_kernel()[0]) ++s->launches;
+  if (rc == QD_OK && last_kernel()[0]) ++s->launches, ++s->trips;
   return rc;
 }
 
 int qd_state_gate_launches(const qd_state* s, int64_t* out) {
   if (!s || !out) return fail(QD_EINVAL, "null argument");
   *out = s->launches;
+  return QD_OK;
+}
+
+int qd_state_gate_trips(const qd_state* s, int64_t* out) {
+  if (!s || !out) return fail(QD_EINVAL, "null argument");
+  *out = s->trips;
   return QD_OK;
 }
 

@@ -500,7 +500,7 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
     GatePlan p;
     plan_gate(r, s->prec, g.t, g.k, g.c, g.v, g.m, g.U, &p);
     int rc = launch_gate(s, p);
-    if (rc == QD_OK && last_kernel()[0]) ++s->launches;
+    if (rc == QD_OK && last_kernel()[0]) ++s->launches, ++s->trips;
     return rc;
   };
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -673,6 +673,7 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
     if (rc) return rc;
     set_last_kernel(dbl ? "k_window<double>" : "k_window<float>");
     s->launches += int64_t(ps.gates.size());   // counted as the passes it stands for
+    ++s->trips;
   }
   return QD_OK;
 }

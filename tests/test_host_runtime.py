@@ -257,3 +257,22 @@ f = Q.qd_fuse(dims, small, 9, 0)
 assert Q.qd_fused_count(f) == 6 and hip.host_waits() <= 2
 Q.qd_fused_free(f)
 """)
+
+
+def test_trips_are_counted_beside_passes(host_runtime):
+    """qd_state_gate_launches counts the passes a list stands for, qd_state_gate_trips the launches made."""
+    host_runtime("""
+dims = (3, 2, 4, 3, 2, 3, 2, 3)
+c = Q.qd_circuit_create(dims)
+for q in (0, 3, 5, 7, 2): Q.qd_circuit_add(c, Q.QD_GATE_F, q)
+s = Q.qd_state_init(dims, Q.QD_C128, 0)
+hip.host_reset()
+Q.qd_circuit_apply(s, c)
+assert (Q.qd_state_gate_launches(s), Q.qd_state_gate_trips(s), len(launches())) == (5, 1, 1)
+hip.host_capture(1)
+Q.qd_circuit_apply(s, c)                                  # recorded one by one
+hip.host_capture(0)
+Q.qd_apply_gate(s, (0,), (), (), Q.qd_gate_matrix(Q.QD_GATE_F, 3, 0))
+assert (Q.qd_state_gate_launches(s), Q.qd_state_gate_trips(s), len(launches())) == (11, 7, 7)
+Q.qd_state_free(s)
+""")
