@@ -345,3 +345,50 @@ def test_large_superoperators_between_small_ones(stream, prec):
     finally:
         Q.qd_state_free(rho)
     assert np.max(np.abs(got - want)) <= (1e-12 if prec == Q.QD_C128 else 4.0 * len(ops) * 256 * 2.0 ** -24)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+def test_operations_in_windows(stream, prec):
+    """Operations that share windows, none composed with the next (their qudits span more than 4): in
+    complex64, where only exact moves change places, the bits of one call for each; in complex128 1e-12."""
+    dims = (3, 3, 3, 2, 3)
+    rng = C.seeded_rng(62)
+    ops = []
+    for i in range(14):
+        q = (0, 1, 2, 4)[i % 4]
+        if i % 3 == 0:
+            ops.append(("gate", C.Gate("X", (q,), ((q + 1) % 3,) if q < 3 else (), (1,) if q < 3 else (), a=1)))
+        elif i % 3 == 1:
+            ops.append(("chan", (q,), Dm.depolarizing(3, 0.1)))
+        else:
+            ops.append(("gate", C.Gate("U", (q,), U=C.haar_unitary(3, rng))))
+    D = int(np.prod(dims))
+    psi = rng.standard_normal(D) + 1j * rng.standard_normal(D)
+    psi /= np.linalg.norm(psi)
+    m0 = np.outer(psi, psi.conj())
+    a, b = Q.qd_density_init(dims, prec, stream), Q.qd_density_init(dims, prec, stream)
+    try:
+        for h in (a, b):
+            Q.qd_state_upload(h, m0.reshape(-1))
+        Q.qd_density_apply_ops(a, ops)
+        assert Q.qd_state_gate_trips(a) <= Q.qd_state_gate_launches(a) // 2
+        for o in ops:
+            if o[0] == "gate":
+                Q.apply_circuit_gate_density(b, o[1], dims)
+            else:
+                Q.qd_density_apply_channel(b, o[1], o[2])
+        ga, gb = download_rho(a, dims), download_rho(b, dims)
+    finally:
+        Q.qd_state_free(a)
+        Q.qd_state_free(b)
+    if prec == Q.QD_C64:
+        assert np.array_equal(ga, gb)
+    else:
+        assert np.max(np.abs(ga - gb)) <= 1e-12
+    want = m0
+    for o in ops:
+        if o[0] == "gate":
+            want = Dm.apply_unitary(want, dims, o[1].targets, o[1].controls, o[1].cvals, O.gate_unitary(o[1], dims))
+        else:
+            want = Dm.apply_channel(want, dims, o[1], o[2])
+    assert np.max(np.abs(ga - want)) <= (1e-12 if prec == Q.QD_C128 else 4.0 * len(ops) * 9 * 2.0 ** -24)

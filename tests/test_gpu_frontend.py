@@ -232,3 +232,118 @@ def test_states_made_and_freed_by_several_threads():
     finally:
         for c in circuits:
             Q.qd_circuit_free(c)
+
+
+def all_windows(dims, n, rng, max_controls=2):
+    """A named circuit whose gates all fit windows, on the lowest and some higher qudits."""
+    c, gates = Q.qd_circuit_create(dims), []
+    qudits = list(range(len(dims)))[-4:] + [0, 1]
+    for i in range(n):
+        q = [int(x) for x in rng.permutation(qudits)]
+        m = int(rng.integers(0, max_controls + 1))
+        kind, t, ctl = "XZF"[i % 3], q[0], q[1:1 + m]
+        val = [int(rng.integers(dims[x])) for x in ctl]
+        a = int(rng.integers(1, dims[t])) if kind == "X" else 0
+        Q.qd_circuit_add(c, {"X": Q.QD_GATE_X, "Z": Q.QD_GATE_Z, "F": Q.QD_GATE_F}[kind], t, a, ctl, val)
+        gates.append(C.Gate(kind, (t,), tuple(ctl), tuple(val), a=a))
+    return c, gates
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("dims", [(3,) * 6, (2,) * 13, (5, 7, 2, 3, 4, 2, 3, 2, 2), (4, 3, 2) * 5])
+def test_lists_that_are_windows(stream, prec, dims):
+    """Lists whose passes are windows, and seen to be: fewer trips than gates, the last kernel k_window. In
+    complex64 they leave the bits of the gates one by one, in complex128 1e-12."""
+    rng = np.random.default_rng(sum(dims) + 3)
+    c, gates = all_windows(dims, 30, rng)
+    D = O.register_size(dims)
+    psi0 = (rng.normal(size=D) + 1j * rng.normal(size=D)) / np.sqrt(2.0 * D)
+    s, one = Q.qd_state_init(dims, prec, stream), Q.qd_state_init(dims, prec, stream)
+    try:
+        for h in (s, one):
+            Q.qd_state_upload(h, psi0)
+        Q.qd_circuit_apply(s, c)
+        assert Q.qd_last_kernel().startswith("k_window")
+        assert Q.qd_state_gate_trips(s) <= 10 and Q.qd_state_gate_launches(s) == len(gates)
+        for g in gates:
+            Q.apply_circuit_gate(one, g, dims)
+        assert Q.qd_state_gate_trips(one) == Q.qd_state_gate_launches(one) == len(gates)
+        a, b = Q.qd_state_download(s), Q.qd_state_download(one)
+    finally:
+        Q.qd_state_free(s)
+        Q.qd_state_free(one)
+        Q.qd_circuit_free(c)
+    if prec == Q.QD_C64:
+        assert np.array_equal(a, b)
+    else:
+        assert max_abs(a, b) <= 1e-12
+
+
+@pytest.mark.parametrize("prec, dims", [(Q.QD_C128, (3,) * 15 + (2,)), (Q.QD_C64, (3,) * 16), (Q.QD_C64, (2,) * 26)])
+def test_windows_of_states_past_the_caches(prec, dims):
+    """States above 256 MB stream through their windows: the same bits (complex64) or 1e-12 (complex128)
+    against the gates one by one."""
+    import torch
+    st = torch.cuda.current_stream().cuda_stream
+    rng = np.random.default_rng(len(dims))
+    c, gates = all_windows(dims, 14, rng)
+    D = O.register_size(dims)
+    dt = torch.complex128 if prec == Q.QD_C128 else torch.complex64
+    assert D * dt.itemsize > 256 << 20
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    a = torch.randn(D, dtype=dt, device="cuda", generator=gen) / D ** 0.5
+    b = a.clone()
+    torch.cuda.synchronize()
+    s = Q.qd_state_wrap(dims, prec, a.data_ptr(), D * dt.itemsize, st)
+    one = Q.qd_state_wrap(dims, prec, b.data_ptr(), D * dt.itemsize, st)
+    try:
+        Q.qd_circuit_apply(s, c)
+        assert Q.qd_last_kernel().startswith("k_window") and Q.qd_state_gate_trips(s) <= 6
+        for g in gates:
+            Q.apply_circuit_gate(one, g, dims)
+        Q.qd_state_sync(one)
+    finally:
+        Q.qd_state_free(s)
+        Q.qd_state_free(one)
+        Q.qd_circuit_free(c)
+    if prec == Q.QD_C64:
+        assert torch.equal(a, b)
+    else:
+        assert float((a - b).abs().max()) <= 1e-12
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("bad", [complex(np.nan, 0.0), complex(0.0, np.inf), complex(-np.inf, np.nan)])
+def test_windows_keep_nan_and_inf_in_their_slices(stream, prec, bad):
+    """A NaN or an infinity reaches exactly the amplitudes that dense gates mix it into; all others keep the
+    bits of the same circuit without it."""
+    dims, touched = (3, 2, 4, 3, 2, 3, 2, 3), (1, 4, 7)
+    rng = np.random.default_rng(4)
+    c = Q.qd_circuit_create(dims)
+    for q in touched:
+        Q.qd_circuit_add(c, Q.QD_GATE_F, q, 0, (), ())
+    D = O.register_size(dims)
+    psi0 = (rng.normal(size=D) + 1j * rng.normal(size=D)) / np.sqrt(2.0 * D)
+    at = 1234
+    out = []
+    try:
+        for x in (psi0[at], bad):
+            psi = psi0.copy()
+            psi[at] = x
+            s = Q.qd_state_init(dims, prec, stream)
+            try:
+                Q.qd_state_upload(s, psi)
+                Q.qd_circuit_apply(s, c)
+                assert Q.qd_last_kernel().startswith("k_window")
+                out.append(Q.qd_state_download(s))
+            finally:
+                Q.qd_state_free(s)
+    finally:
+        Q.qd_circuit_free(c)
+    digits = np.array(np.unravel_index(np.arange(D), dims))
+    same = np.ones(D, bool)
+    for q in range(len(dims)):
+        if q not in touched:
+            same &= digits[q] == digits[q][at]
+    assert not np.isfinite(out[1][same]).any() and np.isfinite(out[0]).all()
+    assert np.array_equal(out[0][~same], out[1][~same])

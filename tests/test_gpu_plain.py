@@ -845,3 +845,32 @@ def test_tiled_small_registers(stream, prec, dims, t, c):
         Q.qd_state_free(s)
     ref = O.apply_gate(psi0, dims, t, c, v, U)
     assert max_abs(out, ref) <= (1e-12 if prec == Q.QD_C128 else c64_tol(1, dT)), (dims, t, c, prec)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C128, Q.QD_C64])
+@pytest.mark.parametrize("dims, t", [((3, 11, 2, 5, 3), (1,)), ((5, 3, 7, 2, 4), (2, 0)), ((2, 17, 5, 2, 3), (1, 2)), ((2, 3, 5, 3, 5), (2, 4))])
+@pytest.mark.parametrize("bad", [complex(np.nan, 0.0), complex(0.0, np.inf)])
+def test_matrix_cores_keep_nan_and_inf_in_their_slices(stream, prec, dims, t, bad):
+    """A NaN or an infinity in one slice of a dense gate reaches the outputs of that slice, all of them, and
+    no other (padded rows, columns and slices of the tile are multiplied by zeros): those keep their bits."""
+    rng = C.seeded_rng(97)
+    D = O.register_size(dims)
+    psi0 = rng.standard_normal(D) + 1j * rng.standard_normal(D)
+    dT = int(np.prod([dims[q] for q in t]))
+    U = C.haar_unitary(dT, rng)
+    digits = np.array(np.unravel_index(np.arange(D), dims))
+    for at in (0, D // 2 + 1, D - 1):
+        out = []
+        for x in (psi0[at], bad):
+            psi = psi0.copy()
+            psi[at] = x
+            s = Q.qd_state_init(dims, prec, stream)
+            try:
+                Q.qd_state_upload(s, psi)
+                Q.qd_apply_gate(s, t, (), (), U)
+                assert Q.qd_last_kernel().startswith("k_dense_mfma")
+                out.append(Q.qd_state_download(s))
+            finally:
+                Q.qd_state_free(s)
+        same = np.all([digits[q] == digits[q][at] for q in range(len(dims)) if q not in t], axis=0)
+        assert not np.isfinite(out[1][same]).any() and np.array_equal(out[0][~same], out[1][~same]), at
