@@ -197,3 +197,57 @@ def test_chunk_sums_four_at_a_time(stream, dims, prec):
         check_all(s, held, dims, shots=4000, seed=5, eps_list=(0.0, 0.5 / np.prod(dims)))
     finally:
         Q.qd_state_free(s)
+
+
+@pytest.mark.parametrize("prec", [Q.QD_C64, Q.QD_C128])
+def test_chunk_sums_over_more_than_one_round(prec):
+    """A register whose chunks take the largest grid (2^20 workgroups of four wavefronts, four chunks each)
+    more than once, the last round ragged (one or two chunks a wavefront): shots and the support list against
+    exact integer sums made piece by piece on the GPU."""
+    import torch
+    dims = (7,) + (4,) * 13 + (3,)                       # 1.41e9 amplitudes, 2^30 are one round
+    D = int(np.prod(dims))
+    assert (1 << 30) + (1 << 28) < D < (1 << 30) + (1 << 29)
+    st = torch.cuda.current_stream().cuda_stream
+    dt = torch.complex64 if prec == Q.QD_C64 else torch.complex128
+    psi = torch.empty(D, dtype=dt, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(31)
+    piece = 1 << 26
+    for a in range(0, D, piece):
+        n = min(piece, D - a)
+        psi[a:a + n] = (torch.randn(n, dtype=dt, device="cuda", generator=gen) / D ** 0.5)
+    torch.cuda.synchronize()
+
+    def probs(a):
+        x = psi[a:a + piece]
+        re, im = x.real.double(), x.imag.double()
+        return re * re + im * im                         # each operation an elementwise pass of its own
+
+    eps = 12.0 / D                                       # e^-12 of the states
+    sums, found = [], []
+    for a in range(0, D, piece):
+        p = probs(a)
+        sums.append(int(torch.round(p * 2.0 ** 62).to(torch.int64).sum()))
+        found.append((p > eps).nonzero().reshape(-1) + a)
+    found = torch.cat(found).cpu().numpy()
+    total = sum(sums)
+    assert total < 1 << 63
+    words = np.random.default_rng(8).integers(0, 2 ** 64, 3000, dtype=np.uint64, endpoint=False)
+    s = Q.qd_state_wrap(dims, prec, psi.data_ptr(), D * psi.element_size(), st)
+    try:
+        got = Q.qd_sample(s, words)
+        idx = Q.qd_support(s, eps)[0]
+    finally:
+        Q.qd_state_free(s)
+    assert len(found) > 1000 and np.array_equal(idx, found)
+    want = np.empty(len(words), np.int64)
+    at = [int(w) * total >> 64 for w in words]
+    before = 0
+    for k, a in enumerate(range(0, D, piece)):
+        mine = [j for j, t in enumerate(at) if before <= t < before + sums[k]]
+        if mine:
+            c = torch.cumsum(torch.round(probs(a) * 2.0 ** 62).to(torch.int64), 0)
+            t = torch.tensor([at[j] - before for j in mine], dtype=torch.int64, device="cuda")
+            want[mine] = (torch.searchsorted(c, t, right=True) + a).cpu().numpy()
+        before += sums[k]
+    assert np.array_equal(got, want)
