@@ -1090,8 +1090,11 @@ static void fill_doff(const GatePlan& p, const int64_t* toff, int64_t* doff) {
 //   - Above it, one slice a thread whose planes begin inside 64-byte sectors: the ends of a wave's runs
 //     share sectors with the next wave's, and a streaming store of part of one costs a whole one.
 //     complex64, where a wave writes 512 bytes, always wins by plain accesses (9 x 9 gates on 3^17 475
-//     and 533 -> 404 and 395 us, a unit of 7^9 148 -> 120); complex128 up to strides of 512 (9 x 9 on
-//     3^16 294 -> 273, a qutrit of stride 27 289 -> 260) and not above (250 -> 272, 745 -> 827 on 3^17).
+//     and 533 -> 404 and 395 us, a unit of 7^9 148 -> 120). complex128 wins up to strides of 512 and not
+//     above, over 150 gates on thirteen registers: plain against streaming 0.79 to 0.95 at 18 to 125, 0.96 to
+//     1.03 at 243 and 343, 0.98 to 1.07 at 625 to 3675, up to 1.13 above (3^16, stride 27, 9 x 9 308 -> 256 us;
+//     stride 729 246 -> 262). Above 2 GB the caches hold the shared sectors for less: 0.94 and 1.01 at 49 and
+//     25, but 1.06 and 1.07 at 343 and 125 (7^10 1922 -> 2032 us, 5^12 1674 -> 1797).
 static bool streaming(const qd_state* s, const GatePlan& p, uint64_t touched, bool direct) {
   const uint64_t amp = uint64_t(amp_bytes(s->prec));
   if (touched * amp <= uint64_t(32) << 20) return true;
@@ -1104,7 +1107,7 @@ static bool streaming(const qd_state* s, const GatePlan& p, uint64_t touched, bo
     sectors = sectors && uint64_t(st) * amp % 64 == 0;
     lowest = std::min(lowest, st);
   }
-  return sectors || (s->prec == QD_C128 && lowest > 512);
+  return sectors || (s->prec == QD_C128 && lowest > (touched * amp > uint64_t(2) << 30 ? 64 : 512));
 }
 
 // tile: the tile of a gate of route QD_ROUTE_TILED, else null

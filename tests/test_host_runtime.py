@@ -276,3 +276,23 @@ Q.qd_apply_gate(s, (0,), (), (), Q.qd_gate_matrix(Q.QD_GATE_F, 3, 0))
 assert (Q.qd_state_gate_launches(s), Q.qd_state_gate_trips(s), len(launches())) == (11, 7, 7)
 Q.qd_state_free(s)
 """)
+
+
+def test_streaming_where_runs_end_inside_sectors(host_runtime):
+    """Direct complex128 gates whose planes begin inside 64-byte sectors: plain accesses up to strides of 512
+    on states up to 2 GB, of 64 above, streaming ones beyond."""
+    host_runtime("""
+def streams(d, n, stride, prec=Q.QD_C128):
+    dims = (d,) * n
+    s = Q.qd_state_init(dims, prec, 0)
+    hip.host_reset()
+    t = n - 1 - round(np.log(stride) / np.log(d))
+    Q.qd_apply_gate(s, (t,), (), (), Q.qd_gate_matrix(Q.QD_GATE_F, d, 0))
+    Q.qd_state_free(s)
+    (name, *_), = launches()
+    assert "k_slices_direct" in name
+    return "Lb1E" in name
+assert not streams(3, 16, 27) and not streams(3, 17, 243) and streams(3, 16, 729)
+assert not streams(7, 10, 49) and streams(7, 10, 343) and streams(5, 12, 125)
+assert not streams(5, 12, 625, Q.QD_C64)
+""")
