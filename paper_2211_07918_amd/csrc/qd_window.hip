@@ -35,7 +35,6 @@ constexpr int kOutCtl = 8;             // controls of one gate outside the windo
 constexpr int kOutDiag = 4;            // diagonal targets of one gate outside the window
 constexpr int kMaxOps = 64;            // gates of one pass
 constexpr int kMaxRuns = 1024;         // runs of a tile
-constexpr int kMaxDiag = 256;          // phases of one diagonal gate
 
 // One gate of a pass, as the kernel's scalar loads read it: two lines of 64 bytes. LDS positions are
 // in bytes (a tile is at most 64 KB). Slice j of the gate is the j-th amplitude of the window whose
@@ -258,12 +257,13 @@ struct Pass {
   uint64_t E = 0;
 };
 
-// Whether some window can hold the gate, whichever of its qudits lie inside: the limits of Op.
+// Whether some window can hold the gate, whichever of its qudits lie inside: the limits of Op (a diagonal
+// gate, all of whose targets may lie inside, has at most 16 phases).
 static bool can_hold(const Register& r, const Gate& p) {
   const GateRef& g = *p.g;
   if (g.m > kOutCtl || g.k + g.m > kInserts) return false;
   if (p.cls != QD_CLASS_DIAGONAL) return slice_size(p.dT);
-  if (g.k > kOutDiag || p.dT > kMaxDiag) return false;
+  if (g.k > kOutDiag) return false;
   for (int sub = 1; sub < 1 << g.k; ++sub) {
     int d = 1;
     for (int j = 0; j < g.k; ++j)
