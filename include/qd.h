@@ -90,10 +90,11 @@ const char* qd_last_error(void);
 /* Name of the kernel instance that the calling thread's last qd_apply_gate / qd_apply_gate_ex
  * launched, e.g. "k_slices_direct<double, 2, DenseOp<double, 2>, 1, plain>" (template arguments:
  * precision, slice size d_T after any control folded into the targets, gate operation, slices per
- * thread and the control mode plain / pred / edge), or that the last block of its last
- * qd_apply_fused launched (e.g. "k_fused_pipe<3, 6, 41, 1, true, 13312>", the template arguments
- * as rocprofv3 prints them); "" when that call launched nothing. Static thread-local storage, for
- * profiling labels; it changes no state. */
+ * thread and the control mode plain / pred / edge), "k_window<double>" or "k_window<float>" where the
+ * last gates of a list shared a pass, or that the last block of its last qd_apply_fused launched (e.g.
+ * "k_fused_pipe<3, 6, 41, 1, true, 13312>", the template arguments as rocprofv3 prints them, or the name
+ * of the gate kernel that a small block runs on); "" when that call launched nothing. Static
+ * thread-local storage, for profiling labels; it changes no state. */
 const char* qd_last_kernel(void);
 
 /* Gate passes made on a state since it was created: one per qd_apply_gate that moved data, one per
@@ -184,6 +185,9 @@ int qd_state_device_ptr(const qd_state* s, void** ptr_out);
 /* Wait for all work queued on the state's stream; QD_EDEVICE reports a deferred fault. */
 int qd_state_sync(const qd_state* s);
 
+/* Waits for the state's stream and releases the state. Its parameter buffer (8 MB, pinned and device) may
+ * stay with the library for a later state: at most four do, none that a graph has recorded, and a device
+ * allocation of the library that finds no room releases them. */
 void qd_state_free(qd_state* s);
 
 /* ---------------------------------------------------------------- gate application (Sec. 2.1) */
@@ -245,6 +249,14 @@ int qd_fused_download_block(const qd_fused* f, int32_t b, double* out);
  *   QD_MODE_FP32_MFMA: complex64 state, FP32 blocks on FP32 matrix cores, FP32 accumulation;
  *   QD_MODE_BF16X3_MFMA: complex64 state, split-BF16 products a_hi b_hi + a_hi b_lo + a_lo b_hi
  *   on BF16 matrix cores with FP32 accumulation.
+ * In both complex64 modes blocks that would leave the matrix-core tiles mostly padding run as one FP32 gate
+ * instead: those of dimension B <= 9, and on registers of 2^22 amplitudes or more B = 12 or 16 where every
+ * window stride is at least QD_TUNE_RUN_MIN and B <= 64 where the tile would be less than 0.4 full (in
+ * QD_MODE_BF16X3_MFMA only for windows above the runs). Blocks of the second kind read their matrix from
+ * the state's parameter buffer: a first such call allocates it (8 MB, pinned and device) where no freed
+ * state has left one, a call waits for the stream when the buffer wraps, and where it cannot be
+ * allocated, and while the stream is captured, those blocks stay on the matrix-core tiles, so that a
+ * captured run can differ from an eager one in the last bits.
  * mode may carry QD_FUSED_RENORMALIZE: after the last block the state is brought back to
  * sum |alpha|^2 = 1 (Eq. (1)) on the GPU, an FP64 reduction of ||psi||^2 (the tree of qd_norm2)
  * followed by a scaling by 1/sqrt(||psi||^2) computed in FP64 on the device, with no host wait (a
@@ -252,7 +264,7 @@ int qd_fused_download_block(const qd_fused* f, int32_t b, double* out);
  * exact in exact arithmetic, so this removes only the drift that rounding of the blocks (held to
  * BF16 pairs in QD_MODE_BF16X3_MFMA) accumulates.
  * QD_EDIM if the register or precision does not match the mode, QD_EINVAL for another flag.
- * Asynchronous. */
+ * Asynchronous, but for the waits named above. */
 int qd_apply_fused(qd_state* s, const qd_fused* f, int32_t mode);
 
 void qd_fused_free(qd_fused* f);
@@ -392,8 +404,11 @@ int qd_circuit_decompose(const qd_circuit* c, qd_circuit** out);
 
 /* Apply the circuit's gates in order to a state of the same register (as qd_apply_gate for each;
  * gates whose targets fit one window of the register share a pass over the state, and gates that
- * commute exactly may change places). QD_EDIM if the registers differ. Asynchronous, like
- * qd_apply_gate. */
+ * commute exactly may change places; in complex64 the state keeps the bits of the gates one by one).
+ * QD_EDIM if the registers differ. Asynchronous, like qd_apply_gate; the tables of shared passes go
+ * through the state's parameter buffer (8 MB, pinned and device, allocated by the first such call where
+ * no freed state has left one), and a call waits for the stream when that wraps. Gates run one by one
+ * where it cannot be allocated, while the stream is captured and on registers of 2^32 amplitudes or more. */
 int qd_circuit_apply(qd_state* s, const qd_circuit* c);
 
 void qd_circuit_free(qd_circuit* c);
@@ -549,7 +564,8 @@ typedef struct {
  * host in FP64: each operation embedded on S (a gate as its controlled unitary, the identity
  * elsewhere), then one pass of the product superoperator on (S, S + n). Passes whose qudits fit one
  * window of the register share one trip over rho, and ones that commute exactly may change places.
- * Asynchronous.
+ * Asynchronous, as qd_circuit_apply is. The operations are composed and applied piece by piece, so that a
+ * call holds at most about 64 MB of composed matrices, or one if that is larger.
  * A call that fails validation leaves rho unchanged; an allocation or launch failure in a later
  * pass of a call (QD_ENOMEM, QD_EDEVICE) can leave rho with the earlier passes applied, as can such
  * a failure in the second pass of a two-pass qd_density_apply_gate. */
@@ -658,8 +674,10 @@ void qd_batch_free(qd_batch* b);
  * workgroup per tile), the most gates qd_batch_apply_layers composes into one operation
  * (QD_TUNE_BATCH_FUSE, 1..8) and the slices per thread of batched slices of 5..9 and of 12..32
  * amplitudes (QD_TUNE_BATCH_SPT_MID, QD_TUNE_BATCH_SPT_WIDE: 1, 2, 4 or 8; 0 keeps the rule of two
- * batches of 16 / d_T slices, at most QD_TUNE_BATCH_SPT). 0 restores the default. Process-wide,
- * host only; QD_EINVAL for an unknown parameter or a value outside its range. */
+ * batches of 16 / d_T slices, at most QD_TUNE_BATCH_SPT). 0 restores the default: tiles of about 9 KB, and
+ * for complex128 gates of d_T <= 4 shapes chosen by stride and size, where a value that is set is what
+ * gates run with. Process-wide, host only; QD_EINVAL for an unknown parameter or a value outside its
+ * range. */
 enum { QD_TUNE_DIRECT_BLOCK = 0, QD_TUNE_DIRECT_SPT = 1, QD_TUNE_TILE_BLOCK = 2,
        QD_TUNE_TILE_ELEMS = 3, QD_TUNE_DIAG_BLOCK = 4, QD_TUNE_BATCH_BLOCK = 5,
        QD_TUNE_BATCH_SPT = 6, QD_TUNE_FUSED_COLS = 7, QD_TUNE_RUN_MIN = 8, QD_TUNE_BATCH_GRID = 9,
@@ -670,7 +688,8 @@ int qd_tune_get(int32_t param, int32_t* value);
 /* Autotuner of the gate kernels: for each stride class of the smallest target stride (1, 2-3,
  * 4-15, 16-255, 256-4095, >= 4096) present in the state's register, times a dense single-qudit gate with
  * every candidate tile shape (direct: 64/128/256 threads x 1/2/4 slices per thread; LDS tile:
- * 512..4096 amplitudes x 128/256 threads) and keeps the fastest per (precision, stride class).
+ * 512..4096 amplitudes x 128/256 threads, those that make different tiles) and keeps the fastest per
+ * (precision, stride class).
  * The state's amplitudes are overwritten: pass a scratch state. Writes the table as JSON to path
  * (NULL = no file). A later qd_tune_set discards the tuned table. Synchronises. */
 int qd_autotune(qd_state* scratch, const char* path);
