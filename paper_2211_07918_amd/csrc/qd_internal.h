@@ -158,6 +158,8 @@ namespace qd {
 // hipMalloc; where there is no room, the spare parameter buffers that freed states left are released first
 hipError_t dev_malloc(void** p, size_t bytes);
 
+bool stream_captured(hipStream_t stream);   // or may be
+
 // Reserve `bytes` in the state's parameter ring, copy `src` there and return the device address.
 // Wrapping around synchronises the stream first so no in-flight copy reads recycled memory.
 int ring_push(qd_state* s, const void* src, size_t bytes, void** dev_out);

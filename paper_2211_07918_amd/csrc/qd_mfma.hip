@@ -1160,8 +1160,7 @@ static bool plain_block(const qd_state* s, const FusedArgs& a, const FusedBlockD
       for (int j = 0; j < d.info.k; ++j) tmin = std::min<int64_t>(tmin, s->reg.strides[d.info.window[j]]);
       plain = plain || tmin >= tune().run_min;
     }
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (plain && (hipStreamIsCapturing(s->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) plain = false;
+    plain = plain && !stream_captured(s->stream);
   }
   return plain;
 }

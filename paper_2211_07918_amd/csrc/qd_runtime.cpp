@@ -459,6 +459,15 @@ hipError_t dev_malloc(void** p, size_t bytes) {
   return e;
 }
 
+// The null stream answers with an error while another thread captures a stream of its own: taken for captured,
+// and not left for the next launch's check to report.
+bool stream_captured(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Gives a ring's buffers back; the stream has finished with them.
 static void ring_leave(ParamRing* r) {
   if (r->host && r->dev && !r->lent && r->cap == kRingBytes) {
@@ -477,11 +486,7 @@ static void ring_leave(ParamRing* r) {
 int ring_reserve(ParamRing* r, hipStream_t stream, size_t bytes, char** host_out, char** dev_out) {
   const size_t align = 256;
   const size_t need = (bytes + align - 1) / align * align;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    r->recorded = true;
-  }
+  if (stream_captured(stream)) r->recorded = true;
   if (!r->host || need > r->cap) {
     if (r->host) {
       // earlier copies and the kernels reading them must finish before the buffers go away

@@ -503,9 +503,7 @@ int apply_gate_list(qd_state* s, const std::vector<GateRef>& list) {
     if (rc == QD_OK && last_kernel()[0]) ++s->launches, ++s->trips;
     return rc;
   };
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (n > 1) (void)hipStreamIsCapturing(s->stream, &cap);
-  if (n < 2 || uint64_t(r.D) > 0xFFFFFFFFull || cap != hipStreamCaptureStatusNone) {
+  if (n < 2 || uint64_t(r.D) > 0xFFFFFFFFull || stream_captured(s->stream)) {
     for (size_t i = 0; i < n; ++i) {
       int rc = alone(i);
       if (rc) return rc;

@@ -82,7 +82,10 @@ int hipMemcpy(void* d, const void* s, size_t n, int) { std::memcpy(d, s, n); ret
 int hipMemcpyAsync(void* d, const void* s, size_t n, int, void*) { std::memcpy(d, s, n); return 0; }
 int hipMemsetAsync(void* d, int v, size_t n, void*) { std::memset(d, v, n); return 0; }
 int hipStreamSynchronize(void*) { ++waits; return 0; }
-int hipStreamIsCapturing(void*, int* s) { *s = capturing; return 0; }
+int hipStreamIsCapturing(void*, int* s) {   // -1: the null stream beside another thread's capture
+  *s = capturing;
+  return capturing < 0 ? last_error = 906 : 0;
+}
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 const char* hipGetErrorString(int) { return "refused by the test"; }
 int hipEventCreate(void** e) { *e = std::malloc(1); return 0; }

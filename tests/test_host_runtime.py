@@ -296,3 +296,28 @@ assert not streams(3, 16, 27) and not streams(3, 17, 243) and streams(3, 16, 729
 assert not streams(7, 10, 49) and streams(7, 10, 343) and streams(5, 12, 125)
 assert not streams(5, 12, 625, Q.QD_C64)
 """)
+
+
+def test_capture_query_that_fails_is_no_launch_error(host_runtime):
+    """Asked whether it is captured, the null stream answers with an error while another thread captures a
+    stream of its own. Lists then run one by one and blocks on their tiles, and the answer is not reported
+    as the error of a launch."""
+    host_runtime("""
+dims = (3, 2, 4, 3, 2, 3, 2, 3)
+c = Q.qd_circuit_create(dims)
+for q in (0, 3, 5, 7, 2): Q.qd_circuit_add(c, Q.QD_GATE_F, q)
+s = Q.qd_state_init(dims, Q.QD_C128, 0)
+big = (3,) * 14
+g = type("G", (), dict(kind="U", targets=(0, 1, 2), controls=(), cvals=(), a=0, U=np.eye(27)))
+f = Q.qd_fuse(big, [g], 27, 0)
+t = Q.qd_state_init(big, Q.QD_C64, 0)
+hip.host_reset()
+hip.host_capture(-1)
+Q.qd_circuit_apply(s, c)
+Q.qd_apply_fused(t, f, Q.QD_MODE_FP32_MFMA)
+Q.qd_apply_gate_ex(s, (1, 3, 5), (), (), np.linalg.qr(np.random.default_rng(1).standard_normal((18, 18)))[0], 1)
+hip.host_capture(0)
+names = [l[0] for l in launches()]
+assert len(names) == 7 and not any("k_window" in n for n in names) and "k_fused" in names[5], names
+Q.qd_state_sync(s)
+""")
