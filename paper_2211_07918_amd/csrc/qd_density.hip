@@ -239,6 +239,25 @@ static std::vector<double> embed_on(const Register& phys, const qd_density_op& o
   return W;
 }
 
+// P = T S, each element summed in ascending l. A row at a time: with a sum for each element this took most of
+// a call's host time, and 20 % more or less by where the compiler had put the loop (24 operations on five
+// qubits 86 to 103 us).
+static void product(const double* __restrict__ T, const double* __restrict__ S, double* __restrict__ P, int N) {
+  for (int r = 0; r < N; ++r) {
+    double* p = P + 2 * size_t(r) * N;
+    std::fill(p, p + 2 * size_t(N), 0.0);
+    for (int l = 0; l < N; ++l) {
+      const double ar = T[2 * (size_t(r) * N + l)], ai = T[2 * (size_t(r) * N + l) + 1];
+      const double* s = S + 2 * size_t(l) * N;
+      for (int c = 0; c < N; ++c) {
+        const double br = s[2 * c], bi = s[2 * c + 1];
+        p[2 * c] += ar * br - ai * bi;
+        p[2 * c + 1] += ar * bi + ai * br;
+      }
+    }
+  }
+}
+
 static int run_list(qd_state* rho, const std::vector<SparseGate>& list) {
   std::vector<GateRef> refs;
   for (const SparseGate& g : list) refs.push_back(ref_of(g));
@@ -571,19 +590,7 @@ int qd_density_apply_ops(qd_state* rho, const qd_density_op* ops, int32_t count,
       const qd_density_op& g = ops[q];
       const std::vector<double> W = embed_on(phys, g, Sq);
       T = superoperator(W.data(), g.kind == QD_OP_GATE ? 1 : g.nk, dT);
-      // P = T * S
-      for (int r = 0; r < N; ++r)
-        for (int c = 0; c < N; ++c) {
-          double re = 0.0, im = 0.0;
-          for (int l = 0; l < N; ++l) {
-            const double ar = T[2 * (size_t(r) * N + l)], ai = T[2 * (size_t(r) * N + l) + 1];
-            const double br = S[2 * (size_t(l) * N + c)], bi = S[2 * (size_t(l) * N + c) + 1];
-            re += ar * br - ai * bi;
-            im += ar * bi + ai * br;
-          }
-          P[2 * (size_t(r) * N + c)] = re;
-          P[2 * (size_t(r) * N + c) + 1] = im;
-        }
+      product(T.data(), S.data(), P.data(), N);
       S.swap(P);
     }
     const std::vector<int32_t> q32(Sq.begin(), Sq.end());
