@@ -7,10 +7,12 @@
 //
 // Why: one gate a pass is bound by HBM on a large state (a gate of d_T <= 4 has 1-4 flops per byte it
 // moves) and by the launch on a small one. A group costs one pass plus, for each gate, one trip through
-// LDS (2 x 16 bytes per amplitude at 128 bytes per clock and CU), which bounds it on a large state; on a
-// small one each gate is a chain of scalar loads, LDS reads and a barrier of about 0.5 us.
+// LDS (2 x 16 bytes per amplitude at 128 bytes per clock and CU) behind a chain of scalar loads, LDS reads
+// and a barrier: of about 0.5 us on a small state; on a large one the LDS pipes are active 30 to 50 % of
+// the time of a long pass and HBM moves 1.5 to 3 TB/s (5.1 in a pass of few gates).
 // Measured, complex128, named gates, one call each before: 200 gates on 2.5e5 amplitudes 1078 -> 207 us,
-// 60 gates on 1.1e8 amplitudes (1.7 GB) 30.0 -> 4.0 ms in 3 passes, 100 gates on 3^15 7.0 -> 1.25 ms; 24 gates with their channels on a density matrix of 2.7e7 elements, kernels 4.5 -> 1.8 ms.
+// 60 gates on 1.1e8 amplitudes (1.7 GB) 30.0 -> 4.0 ms in 3 passes, 100 gates on 3^15 7.0 -> 1.25 ms;
+// 24 gates with their channels on a density matrix of 2.7e7 elements, kernels 4.5 -> 1.8 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -88,7 +90,7 @@ __device__ __forceinline__ uint32_t slice_at(const Op* __restrict__ op, const Re
 }
 
 // One gate on the tile: a thread takes every blockDim-th slice. (Two slices at a time, their reads on
-// their way together, measured 5-10 % slower: LDS bandwidth is the bound, not its latency.)
+// their way together, measured 5-10 % slower.)
 template <typename R, int DT, int KIND>
 __device__ __forceinline__ void gate(unsigned char* lds, const Op* __restrict__ op, const Rest* __restrict__ rest,
                                      const R* __restrict__ m) {
